@@ -93,6 +93,16 @@ const Pattern &polfed_ctx::pattern(int L, bool has_j2) {
   return *p;
 }
 
+const ResTable &polfed_ctx::res_table(int L, bool has_j2, int elem) {
+  auto &p = res_tables[std::make_tuple(L, has_j2 ? 1 : 0, elem)];
+  if (!p) {
+    std::unique_ptr<ResTable> t(new ResTable());
+    build_res_table(L, has_j2, elem, *t);
+    p = std::move(t);
+  }
+  return *p;
+}
+
 const Basis &polfed_ctx::basis(int L) {
   auto &p = bases[L];
   if (!p) {
@@ -178,6 +188,7 @@ int polfed_destroy(polfed_ctx *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   ctx->patterns.clear();
+  ctx->res_tables.clear();
   ctx->bases.clear();
   ctx->bufs.clear();
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);

@@ -214,6 +214,50 @@ struct BatchTables {
   int ints;  // LDS size in int32 words
 };
 
+// resident.hip: the whole Clenshaw filter of a short chain in one launch, one
+// workgroup a column (all K + 1 steps in LDS).
+//
+// Neighbour table of a chain length: the rows sorted by their numbers of J1
+// and J2 neighbours, perm[p] the row at place p; tile q holds places 64 q ..
+// 64 q + 63, its neighbours as np1 (J1) and np2 (J2) words a lane, word k at
+// words[off + 64 k + lane]: two LDS byte offsets (elem bytes a row).
+struct ResTile {
+  int off;
+  short np1, np2;
+};
+struct ResTable {
+  int n = 0, ntile = 0;
+  DevBuf perm, tiles, words;  // uint16 [n], ResTile [ntile], uint32
+};
+void build_res_table(int L, bool has_j2, int elem, ResTable &t);
+// One member of a resident launch: its chain's table, dt = a d + b, an n x
+// ncol block X, the output Y, and scratch of ncol x scratch_per values.  Its
+// columns are the workgroups wg0 .. wg0 + ncol - 1.
+template <class T>
+struct ResItem {
+  const uint16_t *perm;
+  const ResTile *tiles;
+  const uint32_t *words;
+  const T *dt;
+  const T *X;
+  T *Y;
+  T *scratch;
+  const double *coef;  // c_0 .. c_K (device)
+  double Dinv;
+  long long K, ldx, ldy, scratch_per;
+  T w1, w2;    // a J1, a J2
+  T w1f, w2f;  // the last step's: a J1 / (2 D), a J2 / (2 D)
+  int n, ntile, wg0;
+};
+// >= 0 where chains of n rows at elem bytes a value fit the resident filter.
+int resident_form(long long n, int elem);
+long long resident_scratch(long long n, int elem);  // scratch_per
+// The filters of B members of one chain length and bond set: items on the
+// device, or (items null) the one member `one`; total_wg columns in all.
+template <class T>
+void launch_resident(hipStream_t st, const ResItem<T> &one, const ResItem<T> *items, int B,
+                     int total_wg, long long Kmax, int L, bool has_j2);
+
 // Rows per tile of the batched step kernel for this width and shape.
 template <class T>
 long long batched_tile_rows(int S, const StepShape &shape);
@@ -385,6 +429,8 @@ struct polfed_ctx {
   std::string last_error;
   std::map<int, std::unique_ptr<polfed::Basis>> bases;  // per L
   std::map<std::pair<int, int>, std::unique_ptr<polfed::Pattern>> patterns;  // per (L, J2 != 0)
+  // neighbour tables of the resident filter, per (L, J2 != 0, bytes a value)
+  std::map<std::tuple<int, int, int>, std::unique_ptr<polfed::ResTable>> res_tables;
   std::map<std::string, std::unique_ptr<polfed::DevBuf>> bufs;
   // HIP-event timing of the filter kernels (Chebyshev steps), accumulated
   // over a solve: GPU seconds between the first and last step of each
@@ -415,4 +461,5 @@ struct polfed_ctx {
   }
   const polfed::Basis &basis(int L);
   const polfed::Pattern &pattern(int L, bool has_j2);
+  const polfed::ResTable &res_table(int L, bool has_j2, int elem);
 };

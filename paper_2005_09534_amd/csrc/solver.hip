@@ -308,6 +308,109 @@ static bool graph_worthwhile(long long n, int S, long long K) {
   return K >= 16 && K <= (1LL << 17) && (double)n * S * sizeof(T) <= 64.0 * (1 << 20);
 }
 
+// After the last launch of a filter: waits for it and adds its time, steps
+// and algorithmic bytes to the context's counters.
+static void finish_filter_stats(polfed_ctx *ctx, double moved, double steps, double *bytes) {
+  if (bytes) *bytes += moved;
+  PF_HIP(hipEventRecord(ctx->ev_stop, ctx->stream));
+  PF_HIP(hipEventSynchronize(ctx->ev_stop));
+  float ms = 0.0f;
+  PF_HIP(hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop));
+  ctx->filter_gpu_s += 1e-3 * ms;
+  ctx->filter_launches += steps;
+  ctx->filter_bytes += moved;
+}
+
+// Whether the Clenshaw filters of n-row chains, cols columns in all, run in
+// one launch (resident.hip) rather than a launch a step.  Up to L = 14 always
+// (a step of L = 14, s = 8 FP64: 1.3 us against 5.0).  At L = 16 (FP32) a
+// column takes 7.5 us a step (13.5 with J2) on its compute unit, a launch
+// 5.2 us for 8 columns and 8.2 for 64 (10.7 with J2), so there only a batch
+// with more columns than that is better off.  A shape that asks for another
+// rank method than the tables keeps the step kernel.
+template <class T>
+static bool use_resident(const StepShape &shape, int form, long long n, long long cols) {
+  const int f = resident_form(n, (int)sizeof(T));
+  return form == POLFED_FORM_CLENSHAW && shape.rank_incr == 0 && (f > 0 || (f == 0 && cols >= 128));
+}
+
+// The table and sizes of a chain's resident item.
+template <class T>
+static ResItem<T> resident_item(polfed_ctx *ctx, const Chain &c) {
+  const ResTable &t = ctx->res_table(c.L, c.J2 != 0.0, (int)sizeof(T));
+  ResItem<T> it;
+  std::memset(&it, 0, sizeof(it));
+  it.perm = t.perm.as<uint16_t>();
+  it.tiles = t.tiles.as<ResTile>();
+  it.words = t.words.as<uint32_t>();
+  it.n = t.n;
+  it.ntile = t.ntile;
+  it.scratch_per = resident_scratch(t.n, (int)sizeof(T));
+  return it;
+}
+
+template <class T>
+static void run_resident(polfed_ctx *ctx, const Chain &c, const T *dt, double a, int S,
+                         const T *X, long long ldx, T *Y, long long ldy, long long K,
+                         const std::vector<double> &coef, double D) {
+  ResItem<T> it = resident_item<T>(ctx, c);
+  it.scratch = static_cast<T *>(
+      ctx->buf("res_scratch").ensure(sizeof(T) * (size_t)it.scratch_per * S));
+  double *dc = static_cast<double *>(ctx->buf("res_coef").ensure(sizeof(double) * (K + 1)));
+  PF_HIP(hipMemcpyAsync(dc, coef.data(), sizeof(double) * (K + 1), hipMemcpyHostToDevice,
+                        ctx->stream));
+  const double Dinv = 1.0 / D;
+  it.dt = dt;
+  it.X = X;
+  it.ldx = ldx;
+  it.Y = Y;
+  it.ldy = ldy;
+  it.coef = dc;
+  it.Dinv = Dinv;
+  it.K = K;
+  it.w1 = (T)(a * c.J1);
+  it.w2 = (T)(a * c.J2);
+  it.w1f = (T)(0.5 * (a * c.J1) * Dinv);
+  it.w2f = (T)(0.5 * (a * c.J2) * Dinv);
+  PF_HIP(hipEventRecord(ctx->ev_start, ctx->stream));
+  launch_resident<T>(ctx->stream, it, nullptr, 0, S, K, c.L, c.J2 != 0.0);
+}
+
+// The filters of several chains as resident launches, one for each chain
+// length among them: an item a member with its block, filter and X / Y
+// pointers set (resident_item gives the rest), all of one bond set.  `items`
+// (scratch of the caller) has to live until the launches are done.
+template <class T>
+static void run_resident_batch(polfed_ctx *ctx, std::vector<std::pair<int, ResItem<T>>> &mem,
+                               std::vector<ResItem<T>> &items, int S, bool has_j2) {
+  items.clear();
+  if (mem.empty()) return;
+  std::stable_sort(mem.begin(), mem.end(),
+                   [](const auto &x, const auto &y) { return x.first < y.first; });
+  size_t nscr = 0;
+  for (auto &m : mem) nscr += (size_t)m.second.scratch_per * S;
+  T *scr = static_cast<T *>(ctx->buf("res_scratch").ensure(sizeof(T) * nscr));
+  for (size_t i = 0; i < mem.size(); ++i) {
+    ResItem<T> &it = mem[i].second;
+    it.scratch = scr;
+    scr += (size_t)it.scratch_per * S;
+    it.wg0 = (i > 0 && mem[i - 1].first == mem[i].first) ? items.back().wg0 + S : 0;
+    items.push_back(it);
+  }
+  ResItem<T> *dev = static_cast<ResItem<T> *>(
+      ctx->buf("res_items").ensure(sizeof(ResItem<T>) * items.size()));
+  PF_HIP(hipMemcpyAsync(dev, items.data(), sizeof(ResItem<T>) * items.size(),
+                        hipMemcpyHostToDevice, ctx->stream));
+  for (size_t i = 0; i < mem.size();) {
+    size_t e = i;
+    long long Kmax = 0;
+    while (e < mem.size() && mem[e].first == mem[i].first) Kmax = std::max(Kmax, mem[e++].second.K);
+    launch_resident<T>(ctx->stream, items[i], dev + i, (int)(e - i), (int)(e - i) * S, Kmax,
+                       mem[i].first, has_j2);
+    i = e;
+  }
+}
+
 template <class T>
 static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, int S,
                        const T *X, long long ldx, T *Y, long long ldy, long long K,
@@ -322,6 +425,13 @@ static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, i
   }
   double moved = 0.0;
   const int form = ctx->filter_form;
+  if (use_resident<T>(shape, form, n, S)) {
+    run_resident<T>(ctx, c, dt, a, S, X, ldx, Y, ldy, K, coef, D);
+    moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
+                            D, buf3, form, nullptr, false);
+    finish_filter_stats(ctx, moved, (double)(K + 1), bytes);
+    return;
+  }
   // the slice-major copy of X (allocated before any capture)
   T *xpack = nullptr;
   if (form == POLFED_FORM_CLENSHAW && filter_slices(shape, S) > 1)
@@ -390,12 +500,6 @@ static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, i
     moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
                             D, buf3, form, xpack);
   }
-  if (bytes) *bytes += moved;
-  PF_HIP(hipEventRecord(ctx->ev_stop, ctx->stream));
-  PF_HIP(hipEventSynchronize(ctx->ev_stop));
-  float ms = 0.0f;
-  PF_HIP(hipEventElapsedTime(&ms, ctx->ev_start, ctx->ev_stop));
-  ctx->filter_gpu_s += 1e-3 * ms;
   long long launches = K + 1;
   if (form == POLFED_FORM_FORWARD) {  // steps 1 .. last non-zero c_k, at least one
     launches = 1;
@@ -405,8 +509,7 @@ static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, i
         break;
       }
   }
-  ctx->filter_launches += (double)launches;
-  ctx->filter_bytes += moved;
+  finish_filter_stats(ctx, moved, (double)launches, bytes);
 }
 
 // ------------------------------------------------------- chain helpers --
@@ -1535,7 +1638,57 @@ static void refine_batched(polfed_ctx *ctx, std::vector<std::unique_ptr<Realizat
   try {
     for (auto &ch : chunks) {
       const int c0 = ch.first.first, w = ch.first.second;
-      const std::vector<int> &all = ch.second;
+      // members whose chains fit the resident filter, then the others
+      std::vector<int> all;
+      {
+        std::vector<int> res;
+        for (int i : ch.second)
+          (resident_form(rs[i]->n, (int)sizeof(double)) > 0 ? res : all).push_back(i);
+        size_t ncoef = 0, co = 0;
+        for (int i : res) ncoef += rs[i]->coef_r.size();
+        double *coefs = static_cast<double *>(
+            ctx->buf("res_coef").ensure(sizeof(double) * std::max<size_t>(1, ncoef)));
+        std::vector<std::pair<int, ResItem<double>>> mem;
+        double wsum = 0.0;
+        long long Kmax = 0;
+        for (int i : res) {
+          Realization<T> &r = *rs[i];
+          ResItem<double> it = resident_item<double>(ctx, r.c);
+          PF_HIP(hipMemcpyAsync(coefs + co, r.coef_r.data(), sizeof(double) * r.coef_r.size(),
+                                hipMemcpyHostToDevice, st));
+          it.dt = r.dt64b.template as<double>();
+          it.X = r.Vnb.template as<double>() + c0;
+          it.Y = r.URb.template as<double>() + c0;
+          it.ldx = it.ldy = r.ldr;
+          it.coef = coefs + co;
+          it.Dinv = 1.0 / r.D_r;
+          it.w1 = r.a * r.c.J1;
+          it.w2 = r.a * r.c.J2;
+          it.w1f = 0.5 * it.w1 * it.Dinv;
+          it.w2f = 0.5 * it.w2 * it.Dinv;
+          it.K = r.K_r;
+          co += r.coef_r.size();
+          wsum += (double)r.n * (r.K_r + 1);
+          Kmax = std::max(Kmax, r.K_r);
+          mem.emplace_back(r.c.L, it);
+        }
+        if (!mem.empty()) {
+          PF_HIP(hipEventRecord(e0, st));
+          std::vector<ResItem<double>> items;
+          run_resident_batch<double>(ctx, mem, items, w, rs[res[0]]->c.J2 != 0.0);
+          PF_HIP(hipEventRecord(e1, st));
+          PF_HIP(hipEventSynchronize(e1));
+          float ms = 0.0f;
+          PF_HIP(hipEventElapsedTime(&ms, e0, e1));
+          for (int i : res) {
+            Realization<T> &r = *rs[i];
+            const double f = (double)r.n * (r.K_r + 1) / wsum;
+            r.filter_gpu_s += 1e-3 * ms * f;
+            r.filter_launches += (double)(Kmax + 1) * f;
+            r.refine_bytes += batched_filter_bytes<double>(r.n, w, r.K_r, r.coef_r);
+          }
+        }
+      }
       size_t k0 = 0;
       while (k0 < all.size()) {
         size_t k1 = k0, tot = 0;
@@ -1663,7 +1816,6 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
     std::vector<std::unique_ptr<Realization<T>>> rs(B);
     polfed_opts og = o;
     og.block_size = g.first.first;
-    long long Kmax = 0;
     int first_ok = -1;
     for (int i = 0; i < B; ++i) {
       rs[i].reset(new Realization<T>());
@@ -1675,7 +1827,6 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
         rs[i]->done = true;
         continue;
       }
-      Kmax = std::max(Kmax, rs[i]->K);
       if (first_ok < 0) first_ok = i;
     }
     if (first_ok < 0) {  // every member of the group failed in its setup
@@ -1683,29 +1834,53 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
       if (worst == POLFED_OK) worst = POLFED_NOT_CONVERGED;
       continue;
     }
-    // the longest chain of the group names the launch shape
-    int rL = first_ok;
-    for (int i = 0; i < B; ++i)
-      if (!rs[i]->err && rs[i]->c.L > rs[rL]->c.L) rL = i;
+    // members whose filters run as resident launches, and those that share a
+    // launch a step; the longest chain of these names the launch shape
+    std::map<int, int> per_L;
+    for (auto &r : rs)
+      if (!r->err) ++per_L[r->c.L];
+    std::vector<int> resident, stepped;
+    for (int i = 0; i < B; ++i) {
+      if (rs[i]->err) continue;
+      const StepShape shb = batch_shape_for(ctx, rs[i]->c.L, rs[i]->s, rs[i]->fp32);
+      (use_resident<T>(shb, POLFED_FORM_CLENSHAW, rs[i]->n, (long long)per_L[rs[i]->c.L] * rs[i]->s)
+           ? resident
+           : stepped)
+          .push_back(i);
+    }
+    const int S = rs[first_ok]->s;
+    const bool has_j2 = g.first.second != 0;
+    const int NS = (int)stepped.size();
+    int rL = stepped.empty() ? first_ok : stepped[0];
+    for (int i : stepped)
+      if (rs[i]->c.L > rs[rL]->c.L) rL = i;
     const Realization<T> &r0 = *rs[rL];
-    const int S = r0.s;
-    // per-member recurrence buffers, coefficients and descriptors
+    // coefficients of every member; recurrence buffers and descriptors of the
+    // stepped ones
     size_t nbuf = 0, ncoef = 0;
-    for (auto &r : rs) {
-      nbuf += (size_t)3 * r->n * S;
-      ncoef += r->coef.size();
+    long long Kmax = 0;  // of the stepped members
+    for (auto &r : rs) ncoef += r->coef.size();
+    for (int i : stepped) {
+      nbuf += (size_t)3 * rs[i]->n * S;
+      Kmax = std::max(Kmax, rs[i]->K);
     }
     DevBuf cheb, coefs, itemsd;
     cheb.ensure(sizeof(T) * nbuf);
     coefs.ensure(sizeof(double) * ncoef);
-    std::vector<BatchItem<T>> items(B);
-    std::vector<const Chain *> chains(B);
+    std::vector<const double *> coef_at(B);
     size_t co = 0, bo = 0;
     for (int i = 0; i < B; ++i) {
       Realization<T> &r = *rs[i];
+      coef_at[i] = coefs.as<double>() + co;
       PF_HIP(hipMemcpyAsync(coefs.as<double>() + co, r.coef.data(), sizeof(double) * r.coef.size(),
                             hipMemcpyHostToDevice, st));
-      BatchItem<T> &it = items[i];
+      co += r.coef.size();
+    }
+    std::vector<BatchItem<T>> items(NS);
+    std::vector<const Chain *> chains(NS);
+    for (int k = 0; k < NS; ++k) {
+      Realization<T> &r = *rs[stepped[k]];
+      BatchItem<T> &it = items[k];
       std::memset(&it, 0, sizeof(it));
       it.dt = r.dt();
       it.X = r.Xs();
@@ -1713,21 +1888,37 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
       it.buf = cheb.as<T>() + bo;
       it.Y = r.Ys();
       it.ldy = S;
-      it.coef = coefs.as<double>() + co;
+      it.coef = coef_at[stepped[k]];
       it.Dinv = 1.0 / r.D;
       it.w1 = (T)(r.a * r.c.J1);
       it.w2 = (T)(r.a * r.c.J2);
       it.K = r.K;
-      it.active = r.err ? 0 : 1;
-      chains[i] = r.err ? &r0.c : &r.c;
-      if (r.err) it.K = 0;
-      co += r.coef.size();
+      it.active = 1;
+      chains[k] = &r.c;
       bo += (size_t)3 * r.n * S;
     }
+    auto res_member = [&](int i) {
+      Realization<T> &r = *rs[i];
+      ResItem<T> it = resident_item<T>(ctx, r.c);
+      it.dt = r.dt();
+      it.X = r.Xs();
+      it.Y = r.Ys();
+      it.ldx = it.ldy = S;
+      it.coef = coef_at[i];
+      it.Dinv = 1.0 / r.D;
+      it.w1 = (T)(r.a * r.c.J1);
+      it.w2 = (T)(r.a * r.c.J2);
+      // (from the rounded weights, as the batched step kernel takes them)
+      it.w1f = (T)(0.5 * (double)it.w1 * it.Dinv);
+      it.w2f = (T)(0.5 * (double)it.w2 * it.Dinv);
+      it.K = r.K;
+      return std::make_pair(r.c.L, it);
+    };
     const StepShape shape = batch_shape_for(ctx, r0.c.L, S, r0.fp32);
-    const long long total = fill_batch_chains(items, chains, batched_tile_rows<T>(S, shape));
+    const long long total =
+        NS ? fill_batch_chains(items, chains, batched_tile_rows<T>(S, shape)) : 0;
     const BatchTables bt = batch_tables(items, chains);
-    itemsd.ensure(sizeof(BatchItem<T>) * B);
+    itemsd.ensure(sizeof(BatchItem<T>) * std::max(1, NS));
     StepArgs<T> base = base_args<T>(r0.c, r0.dt());
     hipGraphExec_t graph = nullptr;
     hipEvent_t e0, e1;
@@ -1736,24 +1927,34 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
     double gfilter = 0.0, glaunch = 0.0;
     try {
       for (;;) {
-        int nact = 0;
+        int nact = 0, nstep = 0;
+        std::vector<char> act(B, 0);  // members that take part in this block
         for (int i = 0; i < B; ++i) {
-          items[i].active = rs[i]->done ? 0 : 1;
-          if (!rs[i]->done) {
-            rs[i]->filter_X();
-            ++nact;
-          }
+          if (rs[i]->done) continue;
+          act[i] = 1;
+          rs[i]->filter_X();
+          ++nact;
         }
         if (nact == 0) break;
-        PF_HIP(hipMemcpyAsync(itemsd.p, items.data(), sizeof(BatchItem<T>) * B,
-                              hipMemcpyHostToDevice, st));
-        if (!graph && ctx->use_graphs && Kmax <= (1LL << 17)) {
+        for (int k = 0; k < NS; ++k) nstep += items[k].active = act[stepped[k]];
+        long long steps = nstep ? Kmax : 0;
+        std::vector<std::pair<int, ResItem<T>>> res;
+        std::vector<ResItem<T>> res_items;
+        for (int i : resident)
+          if (act[i]) {
+            res.push_back(res_member(i));
+            steps = std::max(steps, rs[i]->K);
+          }
+        if (nstep)
+          PF_HIP(hipMemcpyAsync(itemsd.p, items.data(), sizeof(BatchItem<T>) * NS,
+                                hipMemcpyHostToDevice, st));
+        if (nstep && !graph && ctx->use_graphs && Kmax <= (1LL << 17)) {
           hipGraph_t gr = nullptr;
           PF_HIP(hipStreamBeginCapture(ctx->own_stream, hipStreamCaptureModeThreadLocal));
           try {
             for (long long j = 0; j <= Kmax; ++j)
-              launch_step_batched<T>(ctx->own_stream, S, base, itemsd.as<BatchItem<T>>(), B, j, Kmax,
-                                     total, bt, shape, ctx->num_cu);
+              launch_step_batched<T>(ctx->own_stream, S, base, itemsd.as<BatchItem<T>>(), NS, j,
+                                     Kmax, total, bt, shape, ctx->num_cu);
           } catch (...) {
             hipGraph_t dummy = nullptr;
             (void)hipStreamEndCapture(ctx->own_stream, &dummy);
@@ -1767,11 +1968,12 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
         }
         const double tf0 = now_s();
         PF_HIP(hipEventRecord(e0, st));
-        if (graph) {
+        run_resident_batch<T>(ctx, res, res_items, S, has_j2);
+        if (nstep && graph) {
           PF_HIP(hipGraphLaunch(graph, st));
-        } else {
+        } else if (nstep) {
           for (long long j = 0; j <= Kmax; ++j)
-            launch_step_batched<T>(st, S, base, itemsd.as<BatchItem<T>>(), B, j, Kmax, total,
+            launch_step_batched<T>(st, S, base, itemsd.as<BatchItem<T>>(), NS, j, Kmax, total,
                                    bt, shape, ctx->num_cu);
         }
         PF_HIP(hipEventRecord(e1, st));
@@ -1779,19 +1981,19 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
         float ms = 0.0f;
         PF_HIP(hipEventElapsedTime(&ms, e0, e1));
         gfilter += 1e-3 * ms;
-        glaunch += (double)(Kmax + 1);
+        glaunch += (double)(steps + 1);
         // algorithmic bytes of the active members (same model as one filter)
         for (int i = 0; i < B; ++i)
-          if (items[i].active) rs[i]->bytes += batched_filter_bytes<T>(rs[i]->n, S, rs[i]->K, rs[i]->coef);
+          if (act[i]) rs[i]->bytes += batched_filter_bytes<T>(rs[i]->n, S, rs[i]->K, rs[i]->coef);
         const double tf = now_s() - tf0;
         for (int i = 0; i < B; ++i)
-          if (items[i].active) rs[i]->t_filter += tf / nact;
+          if (act[i]) rs[i]->t_filter += tf / nact;
         // every active member's block, then their convergence checks: the
         // members due at one T_m size run their eigenproblems in one batched
         // launch when small enough
         std::vector<int> due;
         for (int i = 0; i < B; ++i) {
-          if (!items[i].active) continue;
+          if (!act[i]) continue;
           try {
             if (rs[i]->lanczos_block()) due.push_back(i);
           } catch (const Error &e) {
