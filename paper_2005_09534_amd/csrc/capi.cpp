@@ -103,6 +103,16 @@ const ResTable &polfed_ctx::res_table(int L, bool has_j2, int elem) {
   return *p;
 }
 
+const SegTable &polfed_ctx::seg_table(int L) {
+  auto &p = seg_tables[L];
+  if (!p) {
+    std::unique_ptr<SegTable> t(new SegTable());
+    build_seg_table(L, *t);
+    p = std::move(t);
+  }
+  return *p;
+}
+
 const Basis &polfed_ctx::basis(int L) {
   auto &p = bases[L];
   if (!p) {
@@ -189,6 +199,7 @@ int polfed_destroy(polfed_ctx *ctx) {
   (void)hipDeviceSynchronize();
   ctx->patterns.clear();
   ctx->res_tables.clear();
+  ctx->seg_tables.clear();
   ctx->bases.clear();
   ctx->bufs.clear();
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->own_stream);

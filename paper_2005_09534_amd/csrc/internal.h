@@ -258,6 +258,47 @@ template <class T>
 void launch_resident(hipStream_t st, const ResItem<T> &one, const ResItem<T> *items, int B,
                      int total_wg, long long Kmax, int L, bool has_j2);
 
+// segment.hip: the step kernel of the longer chains, by segments (rows that
+// share their bits from kSegM up).
+constexpr int kSegM = 10;
+constexpr int kSegRec = 64;  // ints of a segment's record
+struct SegTable {
+  int nseg = 0;
+  int seg0[4][9];    // first segments of 1, 2, 4, 8 parts of equal row counts
+  DevBuf rec, rows;  // int [nseg * kSegRec]; 32 bytes a low part
+};
+void build_seg_table(int L, SegTable &t);
+// One step (see StepArgs) on slices of the block, *ss bytes from one slice to
+// the next; V and W have their rows next to each other in a slice, X and out
+// *row bytes apart.  W may be out.
+template <class T>
+struct SegArgs {
+  const int *rec;
+  const unsigned char *rows;
+  const T *dt;
+  const T *X, *V, *W;
+  T *out;
+  size_t xss, vss, oss;
+  uint32_t xrow, orow;
+  T alpha, dscale, w1, w2, gamma;
+  int nslices;
+  int lparts;   // the segments fall into 2^lparts parts (1, 2, 4 or 8), an XCD
+  int seg0[9];  // takes one part of a slice: segments seg0[p] .. seg0[p + 1]
+};
+// Columns of a slice of an S-column block, and a step on all slices (rec,
+// rows, nslices, lparts and seg0 are filled in here).
+template <class T>
+int segment_width(int S);
+template <class T>
+void launch_segment(hipStream_t st, int L, bool has_j2, int S, const SegTable &t, SegArgs<T> a);
+// A row-major n x S block to slices (packed, may be null) and beta times it
+// (scaled, may be null); and slices back to row-major.
+template <class T>
+void launch_to_slices(hipStream_t st, long long n, int S, const T *X, long long ldx, T *packed,
+                      T beta, T *scaled);
+template <class T>
+void launch_from_slices(hipStream_t st, long long n, int S, const T *packed, T *Y, long long ldy);
+
 // Rows per tile of the batched step kernel for this width and shape.
 template <class T>
 long long batched_tile_rows(int S, const StepShape &shape);
@@ -429,6 +470,7 @@ struct polfed_ctx {
   std::string last_error;
   std::map<int, std::unique_ptr<polfed::Basis>> bases;  // per L
   std::map<std::pair<int, int>, std::unique_ptr<polfed::Pattern>> patterns;  // per (L, J2 != 0)
+  std::map<int, std::unique_ptr<polfed::SegTable>> seg_tables;  // per L
   // neighbour tables of the resident filter, per (L, J2 != 0, bytes a value)
   std::map<std::tuple<int, int, int>, std::unique_ptr<polfed::ResTable>> res_tables;
   std::map<std::string, std::unique_ptr<polfed::DevBuf>> bufs;
@@ -462,4 +504,5 @@ struct polfed_ctx {
   const polfed::Basis &basis(int L);
   const polfed::Pattern &pattern(int L, bool has_j2);
   const polfed::ResTable &res_table(int L, bool has_j2, int elem);
+  const polfed::SegTable &seg_table(int L);
 };

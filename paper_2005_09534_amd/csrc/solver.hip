@@ -301,6 +301,57 @@ static double queue_filter(hipStream_t stream, int num_cu, const StepShape &shap
   return moved;
 }
 
+// Whether the steps of a chain of length L run by segments (segment.hip):
+// above the resident filter's lengths, unless the shape asks for another rank
+// method than the tables.
+static bool use_segments(const StepShape &shape, int L) {
+  return shape.rank_incr == 0 && L >= kSegM + 4;
+}
+
+// The Clenshaw filter by segments, K >= 1.  buf3 holds b_{k+1} and b_{k+2} =
+// b_k (a step overwrites its own W) and, where the block has more than one
+// slice, X in slices; the last step's slices then go back to row-major Y.
+template <class T>
+static void queue_filter_segments(polfed_ctx *ctx, const Chain &c, const T *dt, double a, int S,
+                                  const T *X, long long ldx, T *Y, long long ldy, long long K,
+                                  const std::vector<double> &coef, double D, T *buf3) {
+  hipStream_t stream = ctx->stream;
+  const long long n = c.basis->n;
+  const SegTable &t = ctx->seg_table(c.L);
+  const int w = segment_width<T>(S);
+  const bool sliced = w < S;
+  T *b[2] = {buf3, buf3 + (size_t)n * S};
+  T *xp = buf3 + (size_t)2 * n * S;
+  const double Dinv = 1.0 / D;
+  // b_K = c_K X
+  launch_to_slices<T>(stream, n, S, X, ldx, sliced ? xp : nullptr, (T)coef[K], b[0]);
+  const uint32_t row = (uint32_t)(w * sizeof(T));
+  for (long long j = 1; j <= K; ++j) {
+    const bool last = j == K;
+    SegArgs<T> s;
+    std::memset(&s, 0, sizeof(s));
+    s.dt = dt;
+    s.V = b[(j - 1) & 1];
+    s.W = (j >= 2) ? b[j & 1] : nullptr;
+    s.out = b[j & 1];
+    s.X = (last || coef[K - j] != 0.0) ? (sliced ? xp : X) : nullptr;
+    s.xrow = sliced ? row : (uint32_t)(ldx * sizeof(T));
+    s.orow = row;
+    s.xss = s.vss = s.oss = (size_t)n * row;
+    if (last && !sliced) {
+      s.out = Y;
+      s.orow = (uint32_t)(ldy * sizeof(T));
+    }
+    s.alpha = last ? (T)(coef[0] * Dinv) : (T)coef[K - j];
+    s.dscale = last ? (T)Dinv : T(2);
+    s.w1 = last ? (T)(0.5 * (a * c.J1) * Dinv) : (T)(a * c.J1);
+    s.w2 = last ? (T)(0.5 * (a * c.J2) * Dinv) : (T)(a * c.J2);
+    s.gamma = last ? (T)(-Dinv) : T(-1);
+    launch_segment<T>(stream, c.L, c.J2 != 0.0, S, t, s);
+  }
+  if (sliced) launch_from_slices<T>(stream, n, S, b[K & 1], Y, ldy);
+}
+
 // Graphs pay off where a step is short (launch-bound): blocks up to 64 MB
 // and K up to 2^17 launches per graph.
 template <class T>
@@ -427,6 +478,15 @@ static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, i
   const int form = ctx->filter_form;
   if (use_resident<T>(shape, form, n, S)) {
     run_resident<T>(ctx, c, dt, a, S, X, ldx, Y, ldy, K, coef, D);
+    moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
+                            D, buf3, form, nullptr, false);
+    finish_filter_stats(ctx, moved, (double)(K + 1), bytes);
+    return;
+  }
+  if (K >= 1 && form == POLFED_FORM_CLENSHAW && use_segments(shape, c.L)) {
+    ctx->seg_table(c.L);
+    PF_HIP(hipEventRecord(ctx->ev_start, ctx->stream));
+    queue_filter_segments<T>(ctx, c, dt, a, S, X, ldx, Y, ldy, K, coef, D, buf3);
     moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
                             D, buf3, form, nullptr, false);
     finish_filter_stats(ctx, moved, (double)(K + 1), bytes);

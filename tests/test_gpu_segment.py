@@ -1,0 +1,69 @@
+"""The step by segments against the step kernel with incremental ranks.
+
+Both add a row's bonds in the same order, so the results are equal bit for
+bit.  Lengths cover every number of high sites a kernel is built for, widths
+every piece size and number of slices.
+"""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pf():
+    from paper_2005_09534_amd import polfed
+    return polfed
+
+
+@pytest.fixture(scope="module")
+def ctx(pf):
+    c = pf.Context(0)
+    yield c
+    c.close()
+
+
+def _both(ctx, L, s, prec, call):
+    """call() by segments and by the step kernel."""
+    saved = ctx.get_step_shape(L, s, prec)
+    Y = call()
+    try:
+        ctx.set_step_shape(L, s, prec, *saved[:5], 1)
+        Z = call()
+    finally:
+        ctx.set_step_shape(L, s, prec, *saved)
+    return Y, Z
+
+
+@pytest.mark.parametrize("L,J2,prec,s", [
+    (L, J2, prec, s) for L in (16, 18, 20) for J2 in (0.0, 0.7) for prec in (0, 1)
+    for s in (1, 2, 4, 8, 64) if not (prec == 0 and s == 4)
+] + [(22, 0.0, 1, 32), (22, 0.7, 0, 16), (24, 0.0, 0, 8), (24, 0.7, 1, 4), (26, 0.0, 1, 16),
+     (26, 0.7, 0, 2), (28, 0.0, 0, 1), (28, 0.7, 1, 2)])
+def test_segments_equal_step_kernel(ctx, pf, L, J2, prec, s):
+    import torch
+    from paper_2005_09534_amd import workloads
+    m = pf.make_model(L, 1.0, J2, 0.9, workloads.fields(L, 2.0, L))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X = torch.randn((pf.dim(L), s), generator=g, device="cuda",
+                    dtype=torch.float64 if prec == 0 else torch.float32)
+    for K in ((1, 2, 9) if L <= 20 else (2,)):
+        for sigma in (0.0, 0.031):  # odd coefficients zero, and none
+            Y, Z = _both(ctx, L, s, prec,
+                         lambda: ctx.apply_filter(m, -40.0, 40.0, sigma, K, X))
+            assert torch.equal(Y, Z), (K, sigma)
+
+
+def test_infinities_stay_where_the_step_kernel_has_them(ctx, pf):
+    import torch
+    from paper_2005_09534_amd import workloads
+    L, s = 16, 4
+    m = pf.make_model(L, 1.0, 0.7, 0.9, workloads.fields(L, 2.0, L))
+    X = torch.from_numpy(workloads.random_block(pf.dim(L), s, 3)).cuda()
+    X[7, 0] = float("inf")
+    X[12000, 1] = float("nan")
+    Y, Z = _both(ctx, L, s, 0, lambda: ctx.apply_filter(m, -40.0, 40.0, 0.031, 2, X))
+    assert torch.equal(torch.isnan(Y), torch.isnan(Z))
+    ok = ~torch.isnan(Z)
+    assert torch.equal(Y[ok], Z[ok])
