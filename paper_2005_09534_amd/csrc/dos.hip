@@ -4,9 +4,12 @@
 // matrix, where the order K is chosen; main text, "POLFED algorithm").
 //
 // Each block of vectors r runs the forward recurrence t_0 = r, t_1 = H~ r,
-// t_{k+1} = 2 H~ t_k - t_{k-1} with the fused step kernel, and after each
-// step a deterministic two-stage reduction takes <t_k, t_k> and
-// <t_k, t_{k-1}> over all rows and columns.  With T_{2k} = 2 T_k^2 - 1 and
+// t_{k+1} = 2 H~ t_k - t_{k-1} with the fused step kernel, and a
+// deterministic two-stage reduction takes <t_k, t_k> and <t_k, t_{k-1}> over
+// all rows and columns.  From L = 16 the steps run by segments (segment.hip)
+// and leave their segments' sums themselves, many steps' sums added up by one
+// launch: L = 20, J1-J2, 4 vectors, a step and its sums took 29.4 us as step,
+// dot and final launches, 10.4 us so.  With T_{2k} = 2 T_k^2 - 1 and
 // T_{2k+1} = 2 T_{k+1} T_k - T_1, m steps give the moments up to 2m:
 //   <r|T_{2k}|r>   = 2 <t_k, t_k> - <r, r>,
 //   <r|T_{2k+1}|r> = 2 <t_{k+1}, t_k> - <t_1, t_0>,
@@ -73,6 +76,32 @@ __global__ __launch_bounds__(64) void k_dual_final(int nblk, const double *part,
   }
 }
 
+// out[2 k .. 2 k + 1] = sums of step k's nblk partial pairs (a workgroup a
+// step: lanes in order, a fixed butterfly, the four waves in order).
+__global__ __launch_bounds__(256) void k_dual_finals(int nblk, const double *part, double *out) {
+  __shared__ double red[2][4];
+  const double *p = part + (size_t)2 * nblk * blockIdx.x;
+  double a0 = 0.0, a1 = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += 256) {
+    a0 += p[2 * b];
+    a1 += p[2 * b + 1];
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    a0 += __shfl_xor(a0, o);
+    a1 += __shfl_xor(a1, o);
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) {
+    red[0][wave] = a0;
+    red[1][wave] = a1;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const double *r = red[threadIdx.x];
+    out[2 * blockIdx.x + threadIdx.x] = ((r[0] + r[1]) + r[2]) + r[3];
+  }
+}
+
 // Columns c < cnt of X (n x ld): x -> -1 where x < 0, else +1.
 __global__ void k_rademacher(long long n, int cnt, double *X, long long ld) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -118,6 +147,17 @@ void dos_moments(polfed_ctx *ctx, const Chain &c, double a, double b, int nmom, 
   }();
   if (shape.rank_incr == 2 && !c.pattern) c.pattern = &ctx->pattern(c.L, c.J2 != 0.0);
 
+  // by segments: sums of up to `hold` steps (64 MB) wait for one final launch
+  const bool seg = shape.rank_incr == 0 && c.L >= kSegM + 4;
+  const SegTable *table = seg ? &ctx->seg_table(c.L) : nullptr;
+  const int w = segment_width<double>(S);
+  const int nseg = seg ? table->nseg * (S / w) : 0;
+  const int hold =
+      seg ? (int)std::max<long long>(1, std::min<long long>(m, (64LL << 20) / (16LL * nseg))) : 0;
+  double *sums = seg ? static_cast<double *>(
+                           ctx->buf("dos_sums").ensure(sizeof(double) * 2 * (size_t)nseg * hold))
+                     : nullptr;
+
   for (int ch = 0; ch < nchunk; ++ch) {
     const int c0 = ch * S;
     const int cnt = std::min(S, nvec - c0);
@@ -133,6 +173,33 @@ void dos_moments(polfed_ctx *ctx, const Chain &c, double a, double b, int nmom, 
     }
     double *d = dots + (size_t)ch * (m + 1) * 2;
     dual_dot(st, tot, t[0], nullptr, part, nblk, d);
+    if (seg) {
+      // t_k overwrites t_{k-2} (two blocks in slices; t[0] was row-major)
+      double *b[2] = {t[1], t[2]};
+      launch_to_slices<double>(st, n, S, t[0], S, b[0], 0.0, nullptr);
+      for (int k = 1; k <= m; ++k) {
+        const int at = (k - 1) % hold;
+        SegArgs<double> sa;
+        std::memset(&sa, 0, sizeof(sa));
+        sa.dt = dt;
+        sa.V = b[(k - 1) & 1];
+        sa.W = (k >= 2) ? b[k & 1] : nullptr;
+        sa.out = b[k & 1];
+        sa.orow = (uint32_t)(w * sizeof(double));
+        sa.vss = sa.oss = (size_t)n * sa.orow;
+        sa.dscale = (k == 1) ? 1.0 : 2.0;
+        sa.w1 = (k == 1 ? 0.5 : 1.0) * a * c.J1;
+        sa.w2 = (k == 1 ? 0.5 : 1.0) * a * c.J2;
+        sa.gamma = -1.0;
+        sa.dots = sums + (size_t)2 * nseg * at;
+        launch_segment<double>(st, c.L, c.J2 != 0.0, S, *table, sa);
+        if (at == hold - 1 || k == m) {
+          k_dual_finals<<<at + 1, 256, 0, st>>>(nseg, sums, d + 2 * (k - at));
+          check_launch("k_dual_finals");
+        }
+      }
+      continue;
+    }
     for (int k = 1; k <= m; ++k) {
       StepArgs<double> sa;
       std::memset(&sa, 0, sizeof(sa));

@@ -281,7 +281,8 @@ struct SegArgs {
   size_t xss, vss, oss;
   uint32_t xrow, orow;
   T alpha, dscale, w1, w2, gamma;
-  int nslices;
+  T *dots;  // FP64, nullable: sums of out^2, out V per (slice, segment)
+  int nslices, nseg;
   int lparts;   // the segments fall into 2^lparts parts (1, 2, 4 or 8), an XCD
   int seg0[9];  // takes one part of a slice: segments seg0[p] .. seg0[p + 1]
 };

@@ -339,7 +339,8 @@ __device__ __forceinline__ void with_count(int c, F &&f) {
 
 // One lane a piece (VE values, at most 16 bytes) of a row.  NH: the most bonds
 // within a high part (L - kSegM - 1).  NT: X, W and out pass the caches by.
-template <class T, int VE, int NH, bool J2, bool NT>
+// DOT: this segment's sums of out^2 and out V go to a.dots as well.
+template <class T, int VE, int NH, bool J2, bool NT, bool DOT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((J2 || NH > 15) ? 5 : 6, 8))) void k_segment(SegArgs<T> a) {
   constexpr int kPiece = VE * (int)sizeof(T);
   __shared__ __align__(16) char tile[256 * kPiece];
@@ -420,6 +421,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((J2 || NH >
   if (in)
     piece_store<T, VE, NT>(scalar_base(a.out, (long long)(slice * a.oss + (size_t)base * a.orow)),
                            i * a.orow, acc);
+  if constexpr (DOT) {
+    // lanes in a fixed butterfly, then the four waves in order
+    __shared__ T red[4][2];
+    T s0 = T(0), s1 = T(0);
+#pragma unroll
+    for (int e = 0; e < VE; ++e) {
+      s0 += in ? acc[e] * acc[e] : T(0);
+      s1 += in ? acc[e] * self[e] : T(0);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      s0 += __shfl_xor(s0, o);
+      s1 += __shfl_xor(s1, o);
+    }
+    if ((tid & 63) == 0) {
+      red[tid >> 6][0] = s0;
+      red[tid >> 6][1] = s1;
+    }
+    __syncthreads();
+    if (tid < 2)
+      a.dots[2 * ((size_t)slice * a.nseg + seg) + tid] =
+          ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+  }
 }
 
 // ------------------------------------------------------------ layout --
@@ -458,6 +482,15 @@ __global__ __launch_bounds__(256) void k_slices(long long n, int S, int w, T *X,
 
 template <class T, int VE, int NH>
 static void launch_one(hipStream_t st, dim3 grid, bool has_j2, bool nt, const SegArgs<T> &a) {
+  if (a.dots) {
+    if constexpr (sizeof(T) == 8)
+      has_j2 ? k_segment<T, VE, NH, true, false, true><<<grid, 256, 0, st>>>(a)
+             : k_segment<T, VE, NH, false, false, true><<<grid, 256, 0, st>>>(a);
+    else
+      throw Error(POLFED_EINVAL, "segment step: sums are FP64");
+    check_launch("k_segment");
+    return;
+  }
   if (has_j2)
     nt ? k_segment<T, VE, NH, true, true><<<grid, 256, 0, st>>>(a)
        : k_segment<T, VE, NH, true, false><<<grid, 256, 0, st>>>(a);
@@ -490,6 +523,7 @@ void launch_segment(hipStream_t st, int L, bool has_j2, int S, const SegTable &t
   const int w = segment_width<T>(S);
   const double n = (double)polfed_dim(L);
   a.nslices = S / w;
+  a.nseg = t.nseg;
   a.rec = t.rec.as<int>();
   a.rows = t.rows.as<unsigned char>();
   // An XCD sweeps a slice of its own where its L2 (4 MB) holds a good part of

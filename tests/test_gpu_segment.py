@@ -67,3 +67,27 @@ def test_infinities_stay_where_the_step_kernel_has_them(ctx, pf):
     assert torch.equal(torch.isnan(Y), torch.isnan(Z))
     ok = ~torch.isnan(Z)
     assert torch.equal(Y[ok], Z[ok])
+
+
+@pytest.mark.parametrize("L,J2,nvec,nmom", [(16, 0.0, 1, 31), (16, 0.7, 3, 32), (18, 0.0, 70, 9),
+                                            (22, 0.7, 40, 80)])  # (more steps than one final sum)
+def test_moments_by_segments(ctx, pf, L, J2, nvec, nmom):
+    """The sums a segment step leaves against those of separate launches: the
+    same terms in another order, n nvec of them of at most 1 (in units of
+    mu_0), so within a few eps sqrt(n nvec) of each other; 1e-12 is 10 times
+    that for the largest."""
+    import numpy as np
+    from paper_2005_09534_amd import workloads
+    m = pf.make_model(L, 1.0, J2, 0.9, workloads.fields(L, 2.0, L))
+    S = 1
+    while S < nvec and S < 64:
+        S *= 2
+    saved = ctx.get_step_shape(L, S, 0)
+    mu = ctx.dos_moments(m, -40.0, 40.0, nmom, nvec=nvec, seed=5)
+    try:
+        ctx.set_step_shape(L, S, 0, *saved[:5], 1)
+        ref = ctx.dos_moments(m, -40.0, 40.0, nmom, nvec=nvec, seed=5)
+    finally:
+        ctx.set_step_shape(L, S, 0, *saved)
+    assert mu[0] == 1.0
+    assert np.abs(mu - ref).max() <= 1e-12
