@@ -17,6 +17,7 @@
 // * Column reductions, Philox4x32-10 start vectors, and the single-vector
 //   Lanczos helpers for the spectral bounds.
 #include "internal.h"
+#include "jacobi_lds.h"
 
 #include <algorithm>
 #include <cmath>
@@ -347,52 +348,17 @@ void launch_symmetrize(hipStream_t st, int s, double *A, int lda) {
 
 // ---------------------------------------------------------------- jacobi --
 //
-// Cyclic Jacobi with the round-robin ("tournament") ordering: with m = n
-// rounded up to even, round r pairs position 0 with position m-1 and k
-// with m-1-k, where position i >= 1 holds index 1 + (i - 1 + r) mod (m-1);
-// over m-1 rounds every pair meets once.  A round computes the n/2
-// rotations from the current A, then applies J^T A J block-wise (each
-// 2 x 2 block of rows {p1,q1} x cols {p2,q2} is owned by one thread) and
-// V <- V J.  The rotation J = [[c, s], [-s, c]] on (p, q) annihilates
-// a_pq with t = sign(th)/(|th| + sqrt(th^2+1)), th = (a_qq - a_pp)/(2 a_pq).
-
-__device__ __forceinline__ int rr_index(int i, int r, int m) {
-  return (i == 0) ? 0 : 1 + (i - 1 + r) % (m - 1);
-}
-
-// Rotation of pair k in round r, computed from the round's input matrix
-// (which no thread of the round writes), so every workgroup that needs it
-// gets the same (p, q, c, s).
-__device__ __forceinline__ void jacobi_rotation(const double *A, int n, int m, int r, int k,
-                                                int &p, int &q, double &c, double &s) {
-  p = rr_index(k, r, m);
-  q = rr_index(m - 1 - k, r, m);
-  if (p > q) {
-    const int t = p;
-    p = q;
-    q = t;
-  }
-  c = 1.0;
-  s = 0.0;
-  if (q < n) {
-    const double apq = A[(size_t)p * n + q];
-    if (apq != 0.0) {
-      const double app = A[(size_t)p * n + p], aqq = A[(size_t)q * n + q];
-      const double th = (aqq - app) / (2.0 * apq);
-      double tt = 1.0 / (fabs(th) + sqrt(th * th + 1.0));
-      if (th < 0.0) tt = -tt;
-      c = 1.0 / sqrt(tt * tt + 1.0);
-      s = tt * c;
-    }
-  }
-}
+// Cyclic Jacobi with the round-robin ordering of jacobi_lds.h.  A round
+// computes the n/2 rotations from the current A, then applies J^T A J
+// block-wise (each 2 x 2 block of rows {p1,q1} x cols {p2,q2} is owned by one
+// thread) and V <- V J.  The rotation J = [[c, s], [-s, c]] on (p, q)
+// annihilates a_pq with t = sign(th)/(|th| + sqrt(th^2+1)), th = (a_qq -
+// a_pp)/(2 a_pq).
 
 // One round over the whole matrix: Aout = J^T Ain J (2 x 2 blocks, one per
 // thread, 16 x 16 pair-blocks per workgroup) and V <- V J in place (16 rows
 // x 16 pairs per workgroup).  Workgroups [0, nta) do A tiles, the rest V.
 constexpr int kJT = 16;
-// Largest matrix the batched LDS Jacobi takes (n^2 doubles + 16 KB of LDS).
-constexpr int kLdsEigMax = 128;
 
 __global__ __launch_bounds__(256) void k_jacobi_round(int n, int r, const double *Ain,
                                                       double *Aout, double *V, int tiles_a) {
@@ -454,123 +420,69 @@ __global__ __launch_bounds__(256) void k_jacobi_round(int n, int r, const double
 }
 
 // Batched cyclic Jacobi for many small symmetric matrices of one size: one
-// workgroup per matrix with the matrix in LDS, the eigenvectors accumulated
-// in global memory.  The rotations (round-robin pairs, same formula as
-// jacobi_rotation), the in-place 2 x 2 block updates and the stopping rule
-// are those of sym_eig, applied to each matrix on its own, so that many
-// Lanczos convergence checks of one batch run in a single launch.
-__global__ __launch_bounds__(1024) void k_jacobi_lds(int n, double *A, double *V, double *w,
-                                                     double *Vout, int max_sweeps) {
-  extern __shared__ double sA[];  // n * n, then 2 * 1024 for reductions
-  __shared__ int sp[kLdsEigMax / 2], sq[kLdsEigMax / 2];
-  __shared__ double sc[kLdsEigMax / 2], ss[kLdsEigMax / 2];
-  __shared__ int s_stop;
-  double *red = sA + (size_t)n * n;
+// workgroup per matrix with the matrix (and, up to kLdsVecMax, the vectors) in
+// LDS.  The rotations, the 2 x 2 block updates and the stopping rule are those
+// of sym_eig, applied to each matrix on its own, so that many Lanczos
+// convergence checks of one batch run in a single launch.
+template <bool VLDS>
+__global__ __launch_bounds__(kEigThreads) void k_jacobi_lds(int n, double *A, double *V, double *w,
+                                                            double *Vout, int max_sweeps) {
+  extern __shared__ double sA[];  // m * ld, kEigRed for reductions, then V (VLDS)
+  __shared__ JacobiRot rot;
+  const int m = eig_even(n), ld = eig_ld(n);
+  double *red = sA + (size_t)m * ld;
+  double *sV = red + kEigRed;
   const int t = threadIdx.x, nt = blockDim.x;
   const size_t nn = (size_t)n * n;
   double *Ab = A + (size_t)blockIdx.x * nn;
   double *Vb = V + (size_t)blockIdx.x * nn;
-  for (size_t e = t; e < nn; e += nt) sA[e] = Ab[e];
-  __syncthreads();
-  const int m = n + (n & 1);
-  const int npair = m / 2;
-  double prev = -1.0;
-  for (int sweep = 0; sweep < max_sweeps && n > 1; ++sweep) {
-    for (int r = 0; r < m - 1; ++r) {
-      if (t < npair) {
-        int p, q;
-        double c, sn;
-        jacobi_rotation(sA, n, m, r, t, p, q, c, sn);
-        sp[t] = p;
-        sq[t] = q;
-        sc[t] = c;
-        ss[t] = sn;
-      }
-      __syncthreads();
-      // A <- J^T A J: the 2 x 2 blocks (pair k1 rows, pair k2 columns) are
-      // disjoint, each read and written by one thread
-      for (int idx = t; idx < npair * npair; idx += nt) {
-        const int k1 = idx / npair, k2 = idx % npair;
-        const int p1 = sp[k1], q1 = sq[k1], p2 = sp[k2], q2 = sq[k2];
-        const double c1 = sc[k1], s1 = ss[k1], c2 = sc[k2], s2 = ss[k2];
-        const bool q1ok = q1 < n, q2ok = q2 < n;
-        const double a00 = sA[(size_t)p1 * n + p2];
-        const double a01 = q2ok ? sA[(size_t)p1 * n + q2] : 0.0;
-        const double a10 = q1ok ? sA[(size_t)q1 * n + p2] : 0.0;
-        const double a11 = (q1ok && q2ok) ? sA[(size_t)q1 * n + q2] : 0.0;
-        const double b00 = c1 * a00 - s1 * a10, b01 = c1 * a01 - s1 * a11;
-        const double b10 = s1 * a00 + c1 * a10, b11 = s1 * a01 + c1 * a11;
-        sA[(size_t)p1 * n + p2] = b00 * c2 - b01 * s2;
-        if (q2ok) sA[(size_t)p1 * n + q2] = b00 * s2 + b01 * c2;
-        if (q1ok) sA[(size_t)q1 * n + p2] = b10 * c2 - b11 * s2;
-        if (q1ok && q2ok) sA[(size_t)q1 * n + q2] = b10 * s2 + b11 * c2;
-      }
-      // V <- V J (columns p, q of every row)
-      for (int idx = t; idx < n * npair; idx += nt) {
-        const int i = idx / npair, k = idx % npair;
-        const int p = sp[k], q = sq[k];
-        if (q >= n) continue;
-        const double c = sc[k], sn = ss[k];
-        const double vp = Vb[(size_t)i * n + p], vq = Vb[(size_t)i * n + q];
-        Vb[(size_t)i * n + p] = c * vp - sn * vq;
-        Vb[(size_t)i * n + q] = sn * vp + c * vq;
-      }
-      __syncthreads();
-    }
-    // off-diagonal and diagonal sums of squares
-    double off = 0.0, dg = 0.0;
-    for (size_t e = t; e < nn; e += nt) {
-      const double v = sA[e];
-      if (e / n == e % n) dg += v * v; else off += v * v;
-    }
-    red[t] = off;
-    red[1024 + t] = dg;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-      if (t < h && t + h < nt) {
-        red[t] += red[t + h];
-        red[1024 + t] += red[1024 + t + h];
-      }
-      __syncthreads();
-    }
-    if (t == 0) {
-      const double o = red[0], d = red[1024];
-      int stop = (!(o > 1e-28 * d) || o == 0.0) ? 1 : 0;
-      if (prev >= 0.0 && sweep >= 3 && o > 0.5 * prev) stop = 1;
-      s_stop = stop;
-      red[0] = o;  // kept for prev
-    }
-    __syncthreads();
-    prev = red[0];
-    const int stop = s_stop;
-    __syncthreads();
-    if (stop) break;
+  for (int e = t; e < m * m; e += nt) {
+    const int i = e / m, j = e % m;
+    const bool in = i < n && j < n;
+    sA[i * ld + j] = in ? Ab[(size_t)i * n + j] : 0.0;
+    if (VLDS && i < n) sV[i * ld + j] = in ? Vb[(size_t)i * n + j] : 0.0;
   }
+  __syncthreads();
+  jacobi_sweeps<VLDS ? kVecLds : kVecGlobal>(n, sA, VLDS ? sV : Vb, red, rot, max_sweeps);
+  __syncthreads();
   // eigenvalues ascending (ties by index) and the matching columns of V
   double *wb = w + (size_t)blockIdx.x * n;
   double *Vo = Vout + (size_t)blockIdx.x * nn;
+  int *rank_of = reinterpret_cast<int *>(red);
   for (int i = t; i < n; i += nt) {
-    const double di = sA[(size_t)i * n + i];
+    const double di = sA[i * ld + i];
     int rank = 0;
     for (int j = 0; j < n; ++j) {
-      const double dj = sA[(size_t)j * n + j];
+      const double dj = sA[j * ld + j];
       rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
     }
     wb[rank] = di;
-    for (int row = 0; row < n; ++row) Vo[(size_t)row * n + rank] = Vb[(size_t)row * n + i];
+    rank_of[i] = rank;
+  }
+  __syncthreads();
+  for (size_t e = t; e < nn; e += nt) {
+    const int row = (int)(e / n), i = (int)(e % n);
+    Vo[(size_t)row * n + rank_of[i]] = VLDS ? sV[row * ld + i] : Vb[e];
   }
 }
 
 bool sym_eig_batched(hipStream_t st, int n, int B, double *A, double *V, double *w,
                      double *Vout) {
   if (n < 1 || n > kLdsEigMax || B < 1) return false;
-  const size_t shm = sizeof(double) * ((size_t)n * n + 2 * 1024);
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(k_jacobi_lds),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess) {
+  const bool vlds = n <= kLdsVecMax;
+  const size_t one = (size_t)eig_even(n) * eig_ld(n);
+  const size_t shm = sizeof(double) * (one * (vlds ? 2 : 1) + kEigRed);
+  const void *kernel = vlds ? reinterpret_cast<const void *>(k_jacobi_lds<true>)
+                            : reinterpret_cast<const void *>(k_jacobi_lds<false>);
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
+      hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  k_jacobi_lds<<<B, 1024, shm, st>>>(n, A, V, w, Vout, 40);
+  if (vlds)
+    k_jacobi_lds<true><<<B, kEigThreads, shm, st>>>(n, A, V, w, Vout, 40);
+  else
+    k_jacobi_lds<false><<<B, kEigThreads, shm, st>>>(n, A, V, w, Vout, 40);
   check_launch("k_jacobi_lds");
   return true;
 }

@@ -13,17 +13,20 @@
 // matrices M_n^T M_n; S_E = -sum lambda ln lambda.
 //
 // Device steps: scatter each (vector, cut) into its blocks (row and column
-// by the colex rank of a and b among patterns of their weight), form the
-// block Gram matrices, take their eigenvalues with the batched LDS Jacobi
-// (all blocks of one size at once; blocks up to 128 x 128, i.e. L <= 18),
-// and sum -lambda ln lambda per (vector, cut).
+// by the colex rank of a and b among patterns of their weight); one workgroup
+// a block forms its Gram matrix, takes its eigenvalues with the LDS Jacobi
+// (blocks up to 128 x 128, i.e. L <= 18) and sums -lambda ln lambda; and the
+// sums of a (vector, cut)'s blocks are added up.
 #include <algorithm>
 #include <cmath>
 #include <vector>
 
 #include "internal.h"
+#include "jacobi_lds.h"
 
 namespace polfed {
+
+constexpr int kEntBlocks = 10;  // L <= 18: weights 0 .. 9
 
 __device__ __forceinline__ int colex_rank(uint32_t pat, int bits, const int32_t *binom) {
   int r = 0, t = 0;
@@ -52,39 +55,71 @@ __global__ void k_ent_scatter(long long n, int L, const uint32_t *states, const 
   out[(size_t)blockIdx.y * n + off[na] + (size_t)rb * d + ra] = V[(size_t)r * ldv + j];
 }
 
-// Gram matrix of block na for every pair: G[p][i][k] = sum_b M[p][b][i] M[p][b][k]
-// (one workgroup per pair).
-__global__ void k_ent_gram(long long n, int d, long long offn, const double *M, double *G) {
-  const int p = blockIdx.x;
-  const double *Mb = M + (size_t)p * n + offn;
-  double *Gb = G + (size_t)p * d * d;
-  for (int e = threadIdx.x; e < d * d; e += blockDim.x) {
-    const int i = e / d, k = e % d;
+// The blocks of one (vector, cut) pair: block q is d x d at offset off.
+struct EntBlocks {
+  int count;
+  int d[kEntBlocks];
+  long long off[kEntBlocks];
+  int slot[kEntBlocks];  // where its sum goes among the pair's count sums
+};
+
+// One workgroup a block: its Gram matrix G[i][k] = sum_b M[b][i] M[b][k] and
+// that matrix's eigenvalues lambda, all in LDS, then part = -sum lambda ln
+// lambda (ascending).  Blocks of every size in one launch, the largest first:
+// one launch a size left most of the chip idle (L = 16, 20 vectors, 8 cuts:
+// 160 workgroups of each of 9 sizes, 4.7 ms in all; 1.15 ms so), with the
+// eigenvectors, which nothing needs, half of each.
+__global__ __launch_bounds__(kEigThreads) void k_ent_blocks(long long n, int pairs, EntBlocks eb,
+                                                            const double *M, double *part) {
+  extern __shared__ double sA[];  // G: m * ld, kEigRed for reductions
+  __shared__ JacobiRot rot;
+  const int q = blockIdx.x / pairs, p = blockIdx.x % pairs;
+  const int d = eb.d[q];
+  const int m = eig_even(d), ld = eig_ld(d);
+  double *red = sA + (size_t)m * ld;
+  const double *Mb = M + (size_t)p * n + eb.off[q];
+  for (int e = threadIdx.x; e < m * m; e += kEigThreads) {
+    const int i = e / m, k = e % m;
     if (k < i) continue;
     double acc = 0.0;
-    for (int bb = 0; bb < d; ++bb) acc += Mb[(size_t)bb * d + i] * Mb[(size_t)bb * d + k];
-    Gb[(size_t)i * d + k] = acc;
-    Gb[(size_t)k * d + i] = acc;
+    if (k < d)
+      for (int b = 0; b < d; ++b) acc += Mb[(size_t)b * d + i] * Mb[(size_t)b * d + k];
+    sA[i * ld + k] = acc;
+    sA[k * ld + i] = acc;
+  }
+  __syncthreads();
+  jacobi_sweeps<kVecNone>(d, sA, nullptr, red, rot, 40);
+  __syncthreads();
+  double *lam = red;
+  for (int i = threadIdx.x; i < d; i += kEigThreads) {
+    const double di = sA[i * ld + i];
+    int rank = 0;
+    for (int j = 0; j < d; ++j) {
+      const double dj = sA[j * ld + j];
+      rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
+    }
+    lam[rank] = di;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < d; i += kEigThreads) {
+    const double l = lam[i];
+    lam[i] = (l > 1e-300) ? l * log(l) : 0.0;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double acc = 0.0;
+    for (int k = 0; k < d; ++k) acc -= lam[k];
+    part[(size_t)p * eb.count + eb.slot[q]] = acc;
   }
 }
 
-__global__ void k_eye_batch(int d, int B, double *V) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (long long)B * d * d) return;
-  const int w = (int)(e % ((long long)d * d));
-  V[e] = (w / d == w % d) ? 1.0 : 0.0;
-}
-
-// S[p] += -sum_k lambda_k ln lambda_k over the d eigenvalues of pair p.
-__global__ void k_ent_sum(int d, int B, const double *w, double *S) {
+// S[p] = sum of pair p's count sums, in order.
+__global__ void k_ent_sum(int count, int pairs, const double *part, double *S) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= B) return;
+  if (p >= pairs) return;
   double acc = 0.0;
-  for (int k = 0; k < d; ++k) {
-    const double lam = w[(size_t)p * d + k];
-    if (lam > 1e-300) acc -= lam * log(lam);
-  }
-  S[p] += acc;
+  for (int k = 0; k < count; ++k) acc += part[(size_t)p * count + k];
+  S[p] = acc;
 }
 
 void entanglement_entropy(hipStream_t st, const Basis &bs, int nvec, const double *V,
@@ -106,45 +141,44 @@ void entanglement_entropy(hipStream_t st, const Basis &bs, int nvec, const doubl
   // pairs in chunks, each chunk's blocks, Gram matrices and eigenvalues
   // within a bounded workspace
   const long long chunk = std::max<long long>(1, std::min<long long>(npairs, 512));
-  // workspace: S per pair, block offsets, cuts, then four 256-byte aligned
-  // regions of n doubles per pair of the chunk
+  // the blocks, largest first
+  EntBlocks eb;
+  eb.count = h + 1;
+  std::vector<int> order(h + 1);
+  for (int k = 0; k <= h; ++k) order[k] = k;
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return d[x] > d[y]; });
+  for (int q = 0; q <= h; ++q) {
+    eb.d[q] = (int)d[order[q]];
+    eb.off[q] = off[order[q]];
+    eb.slot[q] = order[q];
+  }
+  const size_t shm = sizeof(double) * ((size_t)eig_even(eb.d[0]) * eig_ld(eb.d[0]) + kEigRed);
+  PF_REQUIRE(eb.d[0] <= kLdsEigMax, "entanglement: block beyond the batched eigensolver (L <= 18)");
+  PF_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k_ent_blocks),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
+  // workspace: S per pair, block offsets, cuts, then (256-byte aligned) the
+  // sums of a chunk's blocks and n doubles for each of its pairs
   const size_t small = sizeof(double) * npairs + sizeof(long long) * (h + 2) + sizeof(int) * ncut;
-  const size_t per = sizeof(double) * (size_t)n;  // blocks of one pair
-  char *ws = static_cast<char *>(work.ensure(small + 4 * per * chunk + 256));
+  const size_t per = sizeof(double) * ((size_t)n + h + 1);
+  char *ws = static_cast<char *>(work.ensure(small + per * chunk + 256));
   double *dS = reinterpret_cast<double *>(ws);
   long long *doff = reinterpret_cast<long long *>(ws + sizeof(double) * npairs);
   int *dcut = reinterpret_cast<int *>(ws + sizeof(double) * npairs + sizeof(long long) * (h + 2));
-  double *M = reinterpret_cast<double *>(
+  double *part = reinterpret_cast<double *>(
       (reinterpret_cast<uintptr_t>(ws + small) + 255) & ~(uintptr_t)255);
-  double *G = M + (size_t)n * chunk;
-  double *Vs = G + (size_t)n * chunk;
-  double *Vo = Vs + (size_t)n * chunk;
+  double *M = part + (size_t)(h + 1) * chunk;
   PF_HIP(hipMemcpyAsync(doff, off.data(), sizeof(long long) * (h + 2), hipMemcpyHostToDevice, st));
   PF_HIP(hipMemcpyAsync(dcut, cuts.data(), sizeof(int) * ncut, hipMemcpyHostToDevice, st));
-  launch_fill(st, dS, npairs, 0.0);
   for (long long p0 = 0; p0 < npairs; p0 += chunk) {
     const int B = (int)std::min<long long>(chunk, npairs - p0);
     dim3 grid((unsigned)((n + 255) / 256), (unsigned)B);
     k_ent_scatter<<<grid, 256, 0, st>>>(n, L, bs.states.as<uint32_t>(), V, ldv, ncut, dcut,
                                         bs.binom.as<int32_t>(), doff, M, (int)p0);
     check_launch("k_ent_scatter");
-    for (int k = 0; k <= h; ++k) {
-      // block k of every pair: Gram matrices (G), starting vectors (Vs),
-      // eigenvectors and then eigenvalues (Vo): B (dk^2 + dk) <= B n doubles,
-      // as the largest block appears twice in the sector (h >= 3) or fills it
-      const int dk = (int)d[k];
-      k_ent_gram<<<B, 256, 0, st>>>(n, dk, off[k], M, G);
-      check_launch("k_ent_gram");
-      const long long tot = (long long)B * dk * dk;
-      k_eye_batch<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(dk, B, Vs);
-      check_launch("k_eye_batch");
-      double *w = Vo + (size_t)B * dk * dk;
-      if (!sym_eig_batched(st, dk, B, G, Vs, w, Vo))
-        throw Error(POLFED_EINVAL, "entanglement: block of size " + std::to_string(dk) +
-                                       " beyond the batched eigensolver (L <= 18)");
-      k_ent_sum<<<(B + 255) / 256, 256, 0, st>>>(dk, B, w, dS + p0);
-      check_launch("k_ent_sum");
-    }
+    k_ent_blocks<<<(unsigned)(B * eb.count), kEigThreads, shm, st>>>(n, B, eb, M, part);
+    check_launch("k_ent_blocks");
+    k_ent_sum<<<(B + 255) / 256, 256, 0, st>>>(eb.count, B, part, dS + p0);
+    check_launch("k_ent_sum");
   }
   PF_HIP(hipMemcpyAsync(S_host, dS, sizeof(double) * npairs, hipMemcpyDeviceToHost, st));
   PF_HIP(hipStreamSynchronize(st));
