@@ -133,7 +133,7 @@ typedef struct {
   double hv_apps;         /* H~ applications to single vectors              */
   double filter_bytes;    /* algorithmic bytes moved by the filter kernels  */
   double filter_gpu_s;    /* filter kernel time by HIP events on the stream */
-  double filter_launches; /* Chebyshev step kernels launched                */
+  double filter_launches; /* Chebyshev steps run (launches may hold many)   */
 } polfed_info;
 
 /* ---- context ------------------------------------------------------------ */
@@ -323,8 +323,12 @@ int polfed_bounds(polfed_ctx *ctx, const polfed_model *model, int steps,
  * holds more rows of a narrower slice; the Clenshaw filter then keeps its
  * recurrence blocks slice-major; a width that does not split runs
  * unsliced; single H applications and the forward form are never sliced).
- * Results are identical for every shape.  Entries live in the context;
- * without one the library's built-in default is used.  The autotuner
+ * Results are identical for every shape.  With rank_incremental = 0 the
+ * Clenshaw filter chooses its launches by size alone (chains up to L = 14
+ * whole in LDS, longer ones by segments of the basis), and the other fields
+ * are those of the remaining step launches: the forward form and single H
+ * applications.  Entries live in the context; without one the library's
+ * built-in default is used.  The autotuner
  * (paper_2005_09534_amd/autotune.py) searches this space. */
 int polfed_set_step_shape(polfed_ctx *ctx, int L, int nvec, int precision, int threads,
                           int lpl, int wg_per_cu, int lds_tables, int early_loads,
@@ -334,15 +338,14 @@ int polfed_set_step_shape(polfed_ctx *ctx, int L, int nvec, int precision, int t
 int polfed_get_step_shape(polfed_ctx *ctx, int L, int nvec, int precision, int *threads,
                           int *lpl, int *wg_per_cu, int *lds_tables, int *early_loads,
                           int *rank_incremental, int *xcd_slices);
-/* Launch shape of the batched step kernel of polfed_solve_batch (its
- * Lanczos filters and FP64 refinement filters) for a launch whose longest
- * chain has length L, at block width nvec and precision: threads, loads per
- * lane, workgroups per CU, LDS tables, early loads and column slices as in
- * polfed_set_step_shape (the batched kernel always ranks with the tables;
- * the tables of every chain length in a launch go to LDS together).
- * Separate from the single-chain shape: a batched launch walks many chains,
- * where the best shape differs.  Without an entry a built-in default is
- * used (the single-chain default without column slices). */
+/* Launch shape of a batched launch at block width nvec and precision, by the
+ * longest chain's length L: threads, loads per lane, workgroups per CU, LDS
+ * tables, early loads and column slices as in polfed_set_step_shape.  Entries
+ * are checked, kept and reported; the batched filters of polfed_solve_batch
+ * choose their launches by size alone (short chains whole in LDS, the others
+ * by segments of the basis), so an entry changes no result and no time.
+ * Without an entry the built-in default is reported (the single-chain default
+ * without column slices). */
 int polfed_set_batch_shape(polfed_ctx *ctx, int L, int nvec, int precision, int threads,
                            int lpl, int wg_per_cu, int lds_tables, int early_loads,
                            int xcd_slices);
@@ -354,10 +357,11 @@ int polfed_get_batch_shape(polfed_ctx *ctx, int L, int nvec, int precision, int 
  * built-in rule is used (about N_ev/4, capped at 16 in FP64 and 32 in FP32,
  * at 8 for L <= 14). */
 int polfed_set_block_size(polfed_ctx *ctx, int L, int precision, int nev, int block_size);
-/* Capture each filter application (its K+1 step launches) in a HIP graph
- * that is replayed for every Lanczos block (on != 0, the default unless the
- * environment sets POLFED_NO_GRAPH), or launch the steps one by one.  Used
- * where a step is short (blocks up to 64 MB, K <= 2^17).  Results are
+/* Capture each filter application that runs as K+1 launches of the step
+ * kernel (the forward form, and Clenshaw's with rank_incremental 1 or 2) in a
+ * HIP graph that is replayed for every Lanczos block (on != 0, the default
+ * unless the environment sets POLFED_NO_GRAPH), or launch the steps one by
+ * one.  Used where a step is short (blocks up to 64 MB, K <= 2^17).  Results are
  * identical either way. */
 int polfed_set_graphs(polfed_ctx *ctx, int on);
 /* Recurrence that evaluates the filter sum_k c_k T_k(H~) X / D (eq.
@@ -376,7 +380,7 @@ int polfed_set_filter_form(polfed_ctx *ctx, int form);
 int polfed_set_filter_damping(polfed_ctx *ctx, int damping);
 /* Filter counters accumulated by the context since the last reset (or the
  * start of the last polfed_solve): kernel time of the Chebyshev steps by HIP
- * events on the context's stream (seconds), step launches, and algorithmic
+ * events on the context's stream (seconds), steps, and algorithmic
  * bytes (each vector element counted once per stream it is read or
  * written: n [nvec b (streams) + 4 + b] per step, b = 4 or 8).  Any output
  * pointer may be NULL.  reset != 0 zeroes the counters after reading. */
@@ -453,9 +457,10 @@ int polfed_solve(polfed_ctx *ctx, const polfed_model *model,
  * batch of its own; a member whose filter left [-1, 1] is solved again with
  * the bounds margin eta doubled (three times at most), as in polfed_solve.
  * Realisations with one block size and the same J2 != 0
- * share every filter launch whatever their L (one batched step kernel walks
- * all their row tiles), and the FP64 refinement filters of the FP32 mode
- * run batched in the same way.  With opts->block_size = 0 each chain
+ * share their filter launches (chains up to L = 14 and, in FP32 with 128
+ * columns and more, L = 16 run whole filters in one launch a length, the
+ * others share every step's launch whatever their L), and the FP64 refinement
+ * filters of the FP32 mode run batched in the same way.  With opts->block_size = 0 each chain
  * length takes its own block size (polfed_set_block_size, else the
  * built-in rule). */
 int polfed_solve_batch(polfed_ctx *ctx, int R, const polfed_model *models,

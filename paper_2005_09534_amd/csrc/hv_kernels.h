@@ -349,127 +349,6 @@ __global__ __launch_bounds__(MAXT) void k_step(StepArgs<T> a) {
   }
 }
 
-// Batched Clenshaw step for B realisations of one block width S (chain
-// lengths may differ): realisation i has its own chain, diagonal,
-// coefficients, order K_i and buffers.  At global step j (0 <= j <= Kmax),
-// realisation i is at local step j_i = j - (Kmax - K_i) (idle while j_i <
-// 0), so that all end together; step Kmax is the final combination Y = (c_0
-// X + H~ b_1 - b_2)/D.  The tiles of all realisations form one range
-// (realisation-major, item i from its tile0), so an XCD works through whole
-// realisations, and short chains share each launch with long ones.
-template <class T, int S, int LPL, bool LDS_TAB, int MAXT, bool EARLY>
-__global__ __launch_bounds__(MAXT) void k_step_batched(StepArgs<T> base, const BatchItem<T> *items,
-                                                       int B, long long j, long long Kmax,
-                                                       long long ntiles, BatchTables bt) {
-  using C = StepCfg<T, S, LPL>;
-  constexpr int VEC = C::VEC, G = C::G, RPW = C::RPW;
-  extern __shared__ int32_t s_tab[];
-  const int32_t *tC = base.binom;
-  if (LDS_TAB) {  // every distinct chain length's tables
-    for (int k = 0; k < bt.count; ++k) {
-      const int tsz = 1 << bt.half[k];
-      int32_t *sA = s_tab + bt.off[k];
-      uint16_t *sB = reinterpret_cast<uint16_t *>(sA + tsz);
-      for (int i = threadIdx.x; i < tsz; i += blockDim.x) {
-        sA[i] = bt.A[k][i];
-        sB[i] = bt.B[k][i];
-      }
-    }
-    __syncthreads();
-  }
-
-  const long long rows_per_iter = (long long)(blockDim.x >> 6) * RPW;
-  long long t_begin, t_end, t_step;
-  int slice;
-  const int ns = base.nslices;  // column slices: S is one slice's width
-  xcd_tiles(ntiles, ns, slice, t_begin, t_end, t_step);
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int slot = lane / G;
-  const int col = (lane % G) * VEC;
-  // the realisation holding tile t is the last item with tile0 <= t: a
-  // binary search for this group's first tile, then, as t only grows, a
-  // forward scan (the tile range of one realisation spans many steps of t)
-  int i = 0;
-  {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (items[mid].tile0 <= t_begin)
-        lo = mid;
-      else
-        hi = mid - 1;
-    }
-    i = lo;
-  }
-  long long next0 = (i + 1 < B) ? items[i + 1].tile0 : LLONG_MAX;
-  for (long long t = t_begin; t < t_end; t += t_step) {
-    while (t >= next0) {
-      ++i;
-      next0 = (i + 1 < B) ? items[i + 1].tile0 : LLONG_MAX;
-    }
-    const BatchItem<T> it = items[i];
-    const long long ji = j - (Kmax - it.K);
-    if (!it.active || ji < 0) {
-      // the realisation idles at this step: jump past the rest of its tiles
-      // (a batch spends many steps with most of its members idle)
-      if (next0 >= t_end) break;
-      t += ((next0 - t + t_step - 1) / t_step - 1) * t_step;
-      continue;
-    }
-    const long long r = (t - it.tile0) * rows_per_iter + (long long)wave * RPW + slot;
-    if (r >= it.n) continue;
-    StepArgs<T> a = base;
-    a.states = it.states;
-    a.n = it.n;
-    a.L = it.L;
-    a.half = it.half;
-    a.lomask = it.lomask;
-    a.fullmask = it.fullmask;
-    a.dt = it.dt;
-    // recurrence buffers: three blocks of n x (ns S), each slice-major (this
-    // group's slice: n x S at slice n S); X and Y row-major, this slice's
-    // columns at offset slice S
-    const size_t blk = (size_t)it.n * S * ns;
-    const size_t soff = (size_t)slice * it.n * S;
-    T *bufs[3] = {it.buf + soff, it.buf + blk + soff, it.buf + 2 * blk + soff};
-    a.ldv = a.ldw = S;
-    a.ldx = it.ldx;
-    if (j < Kmax) {
-      const long long k = it.K - ji;
-      a.out = bufs[ji % 3];
-      a.ldo = S;
-      a.V = (ji >= 1) ? bufs[(ji - 1) % 3] : nullptr;
-      a.W = (ji >= 2) ? bufs[(ji - 2) % 3] : nullptr;
-      const double ck = it.coef[k];
-      a.X = (ck != 0.0) ? it.X + (size_t)slice * S : nullptr;
-      a.alpha = (T)ck;
-      a.dscale = T(2);
-      a.w1 = it.w1;
-      a.w2 = it.w2;
-      a.gamma = T(-1);
-    } else {
-      a.out = it.Y + (size_t)slice * S;
-      a.ldo = it.ldy;
-      a.X = it.X + (size_t)slice * S;
-      a.alpha = (T)(it.coef[0] * it.Dinv);
-      a.V = (it.K >= 1) ? bufs[(it.K - 1) % 3] : nullptr;
-      a.W = (it.K >= 2) ? bufs[(it.K - 2) % 3] : nullptr;
-      a.dscale = (T)it.Dinv;
-      a.w1 = (T)(0.5 * (double)it.w1 * it.Dinv);
-      a.w2 = (T)(0.5 * (double)it.w2 * it.Dinv);
-      a.gamma = (T)(-it.Dinv);
-    }
-    if (LDS_TAB) {
-      const int32_t *tA = s_tab + it.taboff;
-      step_row<T, S, LPL, EARLY, 0>(a, r, col, tA,
-                                    reinterpret_cast<const uint16_t *>(tA + (1 << it.half)), tC);
-    } else {
-      step_row<T, S, LPL, EARLY, 0>(a, r, col, it.tabA, it.tabB, tC);
-    }
-  }
-}
-
 // Calls f.template operator()<LDS_TAB, MAXT, EARLY, RM>() for the runtime
 // choice (rank modes other than the tables only where the launcher uses
 // them; the stored pattern needs no tables in LDS).
@@ -527,27 +406,6 @@ struct StepLaunch {
 };
 
 template <class T, int S, int LPL>
-struct BatchedLaunch {
-  hipStream_t st;
-  const StepArgs<T> &a;
-  const BatchItem<T> *items;
-  int B;
-  long long j, Kmax, ntiles, nwg;
-  const BatchTables &bt;
-  int threads;
-  size_t shm;
-  template <bool LDS_TAB, int MAXT, bool EARLY, int RM>
-  void operator()() const {
-    if (LDS_TAB && shm > 65536)
-      PF_HIP(hipFuncSetAttribute(
-          reinterpret_cast<const void *>(k_step_batched<T, S, LPL, LDS_TAB, MAXT, EARLY>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
-    k_step_batched<T, S, LPL, LDS_TAB, MAXT, EARLY>
-        <<<(unsigned)nwg, threads, LDS_TAB ? shm : 0, st>>>(a, items, B, j, Kmax, ntiles, bt);
-  }
-};
-
-template <class T, int S, int LPL>
 static void launch_step_s(hipStream_t st, const StepArgs<T> &a0, const StepShape &shape,
                           int num_cu) {
   using C = StepCfg<T, S, LPL>;
@@ -570,21 +428,6 @@ static void launch_step_s(hipStream_t st, const StepArgs<T> &a0, const StepShape
   dispatch_shape<true>(lds, threads, shape.early_loads != 0, mode,
                        StepLaunch<T, S, LPL>{st, a, nwg, threads, shm});
   check_launch("k_step");
-}
-
-template <class T, int S, int LPL>
-static void launch_batched_s(hipStream_t st, const StepArgs<T> &a, const BatchItem<T> *items,
-                             int B, long long j, long long Kmax, long long ntiles,
-                             const BatchTables &bt, const StepShape &shape, int num_cu) {
-  const int threads = shape.threads;
-  long long nwg = std::min((long long)num_cu * shape.wg_per_cu, ntiles * a.nslices);
-  nwg = ((nwg + 7) / 8) * 8;
-  const bool lds = shape.lds_tables && bt.count > 0;
-  const size_t shm = lds ? sizeof(int32_t) * (size_t)bt.ints : 0;
-  dispatch_shape<false>(lds, threads, shape.early_loads != 0, 0,
-                        BatchedLaunch<T, S, LPL>{st, a, items, B, j, Kmax, ntiles, nwg, bt,
-                                                 threads, shm});
-  check_launch("k_step_batched");
 }
 
 // Loads per lane beyond what a row of S values holds change nothing (the
@@ -627,80 +470,6 @@ void launch_step(hipStream_t st, int S, const StepArgs<T> &a0, const StepShape &
     case 16: launch_step_lpl<T, 16>(st, a, shape, num_cu); break;
     case 32: launch_step_lpl<T, 32>(st, a, shape, num_cu); break;
     case 64: launch_step_lpl<T, 64>(st, a, shape, num_cu); break;
-    default: throw Error(POLFED_EINVAL, "block width must be a power of two in [1, 64]");
-  }
-}
-
-template <class T>
-void launch_step_batched(hipStream_t st, int S, const StepArgs<T> &a, const BatchItem<T> *items,
-                         int B, long long j, long long Kmax, long long total_tiles,
-                         const BatchTables &tables, const StepShape &shape, int num_cu) {
-  if (total_tiles <= 0 || B <= 0) return;
-  if (shape.threads != 256 && shape.threads != 512 && shape.threads != 1024)
-    throw Error(POLFED_EINVAL, "step kernel: threads must be 256, 512 or 1024");
-  const int ns = shape.xcd_slices;
-  if (ns != 1 && ns != 2 && ns != 4 && ns != 8)
-    throw Error(POLFED_EINVAL, "step kernel: column slices must be 1, 2, 4 or 8");
-  if (S % ns != 0) throw Error(POLFED_EINVAL, "step kernel: width not divisible by slices");
-  StepArgs<T> a0 = a;
-  a0.nslices = ns;
-  S /= ns;  // the kernel's template width is one slice
-#define PF_BATCH_CASE(SS)                                                                  \
-  case SS: {                                                                               \
-    constexpr int M = max_lpl<T, SS>();                                                    \
-    const int lpl = std::min(shape.lpl, M);                                                \
-    if constexpr (M >= 4)                                                                  \
-      if (lpl == 4) {                                                                      \
-        launch_batched_s<T, SS, 4>(st, a0, items, B, j, Kmax, total_tiles, tables, shape,   \
-                                   num_cu);                                                \
-        break;                                                                             \
-      }                                                                                    \
-    if constexpr (M >= 2)                                                                  \
-      if (lpl == 2) {                                                                      \
-        launch_batched_s<T, SS, 2>(st, a0, items, B, j, Kmax, total_tiles, tables, shape,   \
-                                   num_cu);                                                \
-        break;                                                                             \
-      }                                                                                    \
-    launch_batched_s<T, SS, 1>(st, a0, items, B, j, Kmax, total_tiles, tables, shape,       \
-                               num_cu);                                                    \
-    break;                                                                                 \
-  }
-  switch (S) {
-    PF_BATCH_CASE(1)
-    PF_BATCH_CASE(2)
-    PF_BATCH_CASE(4)
-    PF_BATCH_CASE(8)
-    PF_BATCH_CASE(16)
-    PF_BATCH_CASE(32)
-    PF_BATCH_CASE(64)
-    default: throw Error(POLFED_EINVAL, "block width must be a power of two in [1, 64]");
-  }
-#undef PF_BATCH_CASE
-}
-
-// Rows per tile of the batched kernel: the workgroup's waves times the rows
-// a wave covers at the loads per lane the launcher picks for this width
-// (split into the shape's column slices).
-template <class T>
-long long batched_tile_rows(int S, const StepShape &shape) {
-  if (shape.xcd_slices > 1 && S % shape.xcd_slices == 0) S /= shape.xcd_slices;
-  auto rows = [&](auto s_c) -> long long {
-    constexpr int SS = decltype(s_c)::value;
-    constexpr int M = max_lpl<T, SS>();
-    const int lpl = std::min(shape.lpl, M);
-    const int rpw = (lpl >= 4 && M >= 4) ? StepCfg<T, SS, (M >= 4 ? 4 : 1)>::RPW
-                    : (lpl >= 2 && M >= 2) ? StepCfg<T, SS, (M >= 2 ? 2 : 1)>::RPW
-                                           : StepCfg<T, SS, 1>::RPW;
-    return (long long)(shape.threads / 64) * rpw;
-  };
-  switch (S) {
-    case 1: return rows(std::integral_constant<int, 1>{});
-    case 2: return rows(std::integral_constant<int, 2>{});
-    case 4: return rows(std::integral_constant<int, 4>{});
-    case 8: return rows(std::integral_constant<int, 8>{});
-    case 16: return rows(std::integral_constant<int, 16>{});
-    case 32: return rows(std::integral_constant<int, 32>{});
-    case 64: return rows(std::integral_constant<int, 64>{});
     default: throw Error(POLFED_EINVAL, "block width must be a power of two in [1, 64]");
   }
 }

@@ -173,47 +173,6 @@ struct StepShape {
 template <class T>
 void launch_step(hipStream_t st, int S, const StepArgs<T> &a, const StepShape &shape, int num_cu);
 
-// One realisation of a batched filter (device-resident descriptor).  The
-// realisations of one launch share the block width and whether J2 != 0;
-// each brings its own chain length and basis.
-template <class T>
-struct BatchItem {
-  const T *dt;         // a d + b
-  const T *X;          // n x S input block (leading dimension ldx)
-  T *buf;              // 3 n x S recurrence buffers (leading dimension S)
-  T *Y;                // n x S output (leading dimension ldy)
-  const double *coef;  // c_0 .. c_K (device)
-  double Dinv;         // 1 / D
-  T w1, w2;            // a J1, a J2
-  long long K;
-  int active;
-  // the realisation's chain: Sz=0 states and rank tables, dimension, L
-  const uint32_t *states;
-  const int32_t *tabA;
-  const uint16_t *tabB;
-  long long n;
-  int L, half;
-  uint32_t lomask, fullmask;
-  long long ldx, ldy;
-  // first row tile of this realisation in the launch's tile range (tiles of
-  // batched_tile_rows rows, realisations in item order)
-  long long tile0;
-  int taboff;  // int32 offset of its tables in the launch's LDS staging (BatchTables.off)
-};
-
-// The distinct rank tables of a batched launch (one per chain length), all
-// staged in LDS: set k at int32 offset off[k] (tabA, then tabB as uint16).
-// count = 0: every realisation reads its own tables from global memory.
-constexpr int kMaxBatchTables = 8;
-struct BatchTables {
-  const int32_t *A[kMaxBatchTables];
-  const uint16_t *B[kMaxBatchTables];
-  int half[kMaxBatchTables];
-  int off[kMaxBatchTables];
-  int count;
-  int ints;  // LDS size in int32 words
-};
-
 // resident.hip: the whole Clenshaw filter of a short chain in one launch, one
 // workgroup a column (all K + 1 steps in LDS).
 //
@@ -292,6 +251,30 @@ template <class T>
 int segment_width(int S);
 template <class T>
 void launch_segment(hipStream_t st, int L, bool has_j2, int S, const SegTable &t, SegArgs<T> a);
+// One member of a batched filter by segments: its recurrence blocks b0, b1 (in
+// slices, ss bytes apart), X (xrow bytes from row to row, slices ss apart
+// where it is in slices) and, where the block is one slice, the rows of Y
+// (orow bytes apart; 0: the last step stays in b0 / b1).
+template <class T>
+struct SegItem {
+  const int *rec;
+  const T *dt;
+  const T *X;
+  T *Y, *b0, *b1;
+  const double *coef;  // c_0 .. c_K (device)
+  double Dinv;
+  long long K;
+  size_t ss;
+  uint32_t xrow, orow;
+  T w1, w2, w1f, w2f;  // a J1, a J2, and the last step's, over 2 D
+};
+// The task list of the members' tables: eight parts of `per` tasks.
+void segment_tasks(const std::vector<const SegTable *> &tables, int nslices,
+                   std::vector<int2> &tasks, int &per);
+template <class T>
+void launch_segment_batch(hipStream_t st, int Lmax, bool has_j2, int S, const SegItem<T> *items,
+                          const int2 *tasks, int per, const unsigned char *rows, long long j,
+                          long long Kmax);
 // A row-major n x S block to slices (packed, may be null) and beta times it
 // (scaled, may be null); and slices back to row-major.
 template <class T>
@@ -300,18 +283,6 @@ void launch_to_slices(hipStream_t st, long long n, int S, const T *X, long long 
 template <class T>
 void launch_from_slices(hipStream_t st, long long n, int S, const T *packed, T *Y, long long ldy);
 
-// Rows per tile of the batched step kernel for this width and shape.
-template <class T>
-long long batched_tile_rows(int S, const StepShape &shape);
-
-// One batched Clenshaw step j (0..Kmax) for the B realisations of items
-// (device array, tile0 filled for batched_tile_rows; total_tiles = the
-// tiles of all of them).  a: the launch's common arguments (has_j2, binom);
-// tables: the rank tables staged in LDS (count 0: none).
-template <class T>
-void launch_step_batched(hipStream_t st, int S, const StepArgs<T> &a, const BatchItem<T> *items,
-                         int B, long long j, long long Kmax, long long total_tiles,
-                         const BatchTables &tables, const StepShape &shape, int num_cu);
 // Built-in default shapes (used when the context holds no tuned entry) of
 // the single-chain and the batched step kernel.
 StepShape default_shape(int L, int S, bool fp32);

@@ -340,15 +340,9 @@ __device__ __forceinline__ void with_count(int c, F &&f) {
 // One lane a piece (VE values, at most 16 bytes) of a row.  NH: the most bonds
 // within a high part (L - kSegM - 1).  NT: X, W and out pass the caches by.
 // DOT: this segment's sums of out^2 and out V go to a.dots as well.
-template <class T, int VE, int NH, bool J2, bool NT, bool DOT = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((J2 || NH > 15) ? 5 : 6, 8))) void k_segment(SegArgs<T> a) {
+template <class T, int VE, int NH, bool J2, bool NT, bool DOT>
+__device__ __forceinline__ void segment_step(const SegArgs<T> &a, int slice, int seg, char *tile) {
   constexpr int kPiece = VE * (int)sizeof(T);
-  __shared__ __align__(16) char tile[256 * kPiece];
-  const int x = blockIdx.x & 7;
-  const int part = x & ((1 << a.lparts) - 1);
-  const int slice = ((int)blockIdx.y << (3 - a.lparts)) + (x >> a.lparts);
-  const int seg = __builtin_amdgcn_readfirstlane(a.seg0[part] + (int)(blockIdx.x >> 3));
-  if (slice >= a.nslices || seg >= a.seg0[part + 1]) return;
   SegRecord<NH, J2> r;
   r.read(a.rec, seg);
   const int tid = threadIdx.x;
@@ -446,6 +440,65 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((J2 || NH >
   }
 }
 
+// (24 and more registers short of 128: six waves a SIMD, five with J2, hide
+// the round of loads better than four with every neighbour in flight)
+#define PF_SEG_KERNEL(J2, NH) \
+  __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(((J2) || (NH) > 15) ? 5 : 6, 8)))
+
+template <class T, int VE, int NH, bool J2, bool NT, bool DOT = false>
+PF_SEG_KERNEL(J2, NH) void k_segment(SegArgs<T> a) {
+  __shared__ __align__(16) char tile[256 * VE * (int)sizeof(T)];
+  const int x = blockIdx.x & 7;
+  const int part = x & ((1 << a.lparts) - 1);
+  const int slice = ((int)blockIdx.y << (3 - a.lparts)) + (x >> a.lparts);
+  const int seg = __builtin_amdgcn_readfirstlane(a.seg0[part] + (int)(blockIdx.x >> 3));
+  if (slice >= a.nslices || seg >= a.seg0[part + 1]) return;
+  segment_step<T, VE, NH, J2, NT, DOT>(a, slice, seg, tile);
+}
+
+// Global step j of the batched Clenshaw filter (members end together at step
+// Kmax; one of order K_i is idle before step Kmax - K_i + 1).  A workgroup's
+// member, slice and segment stand in the task list: XCD x takes the x-th of
+// its eight parts.
+template <class T, int VE, int NH, bool J2>
+PF_SEG_KERNEL(J2, NH) void k_segment_batch(const SegItem<T> *items, const int2 *tasks, int per,
+                                           const unsigned char *rows, long long j,
+                                           long long Kmax) {
+  __shared__ __align__(16) char tile[256 * VE * (int)sizeof(T)];
+  typedef const __attribute__((address_space(4))) int *Ci;
+  const Ci task = (Ci)(uintptr_t)(tasks + (size_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3));
+  const int who = task[0], seg = task[1];
+  if (seg < 0) return;  // (the list's parts are filled up)
+  const int slice = who >> 20;
+  // (read with scalar loads)
+  typedef const __attribute__((address_space(4))) SegItem<T> *Item;
+  const Item it = (Item)(uintptr_t)(items + (who & 0xfffff));
+  const long long K = it->K, ji = j - (Kmax - K);
+  if (ji < 1) return;
+  const bool last = ji == K;
+  typedef const __attribute__((address_space(4))) double *Cd;
+  const double c = ((Cd)(uintptr_t)it->coef)[K - ji];
+  const double Dinv = it->Dinv;
+  SegArgs<T> a;
+  a.rec = it->rec;
+  a.rows = rows;
+  a.dt = it->dt;
+  a.V = (ji & 1) ? it->b0 : it->b1;
+  a.W = ji >= 2 ? ((ji & 1) ? it->b1 : it->b0) : nullptr;
+  const bool to_y = last && it->orow != 0;
+  a.out = to_y ? it->Y : (ji & 1) ? it->b1 : it->b0;
+  a.orow = to_y ? it->orow : (uint32_t)(VE * sizeof(T));
+  a.X = (last || c != 0.0) ? it->X : nullptr;
+  a.xrow = it->xrow;
+  a.xss = a.vss = a.oss = it->ss;
+  a.alpha = last ? (T)(c * Dinv) : (T)c;
+  a.dscale = last ? (T)Dinv : T(2);
+  a.w1 = last ? it->w1f : it->w1;
+  a.w2 = last ? it->w2f : it->w2;
+  a.gamma = last ? (T)(-Dinv) : T(-1);
+  segment_step<T, VE, NH, J2, false, false>(a, slice, seg, tile);
+}
+
 // ------------------------------------------------------------ layout --
 
 // X (n x S, row-major, leading dimension ldx) to slices of w columns, and
@@ -513,6 +566,45 @@ static void launch_nh(hipStream_t st, int L, dim3 grid, bool has_j2, bool nt, co
     launch_one<T, VE, 19>(st, grid, has_j2, nt, a);
 }
 
+template <class T, int VE>
+static void launch_batch_nh(hipStream_t st, int L, bool has_j2, unsigned grid,
+                            const SegItem<T> *items, const int2 *tasks, int per,
+                            const unsigned char *rows, long long j, long long Kmax) {
+  auto go = [&](auto nh) {
+    constexpr int NH = decltype(nh)::value;
+    if (has_j2)
+      k_segment_batch<T, VE, NH, true><<<grid, 256, 0, st>>>(items, tasks, per, rows, j, Kmax);
+    else
+      k_segment_batch<T, VE, NH, false><<<grid, 256, 0, st>>>(items, tasks, per, rows, j, Kmax);
+  };
+  const int nh = L - kSegM - 1;
+  if (nh <= 7)
+    go(std::integral_constant<int, 7>{});
+  else if (nh <= 11)
+    go(std::integral_constant<int, 11>{});
+  else if (nh <= 15)
+    go(std::integral_constant<int, 15>{});
+  else
+    go(std::integral_constant<int, 19>{});
+  check_launch("k_segment_batch");
+}
+
+template <class T>
+void launch_segment_batch(hipStream_t st, int Lmax, bool has_j2, int S, const SegItem<T> *items,
+                          const int2 *tasks, int per, const unsigned char *rows, long long j,
+                          long long Kmax) {
+  if (per <= 0) return;
+  const int w = segment_width<T>(S);
+  constexpr int F = 16 / (int)sizeof(T);
+  const unsigned grid = 8u * (unsigned)per;
+  if (w == F)
+    launch_batch_nh<T, F>(st, Lmax, has_j2, grid, items, tasks, per, rows, j, Kmax);
+  else if (w == 2)
+    launch_batch_nh<T, 2>(st, Lmax, has_j2, grid, items, tasks, per, rows, j, Kmax);
+  else
+    launch_batch_nh<T, 1>(st, Lmax, has_j2, grid, items, tasks, per, rows, j, Kmax);
+}
+
 template <class T>
 int segment_width(int S) {
   return std::min(S, 16 / (int)sizeof(T));
@@ -578,9 +670,46 @@ void launch_from_slices(hipStream_t st, long long n, int S, const T *packed, T *
   slices<T, true>(st, n, S, Y, ldy, const_cast<T *>(packed), T(0), nullptr);
 }
 
+// Every XCD's share of the members' (slice, segment) pairs: below 64 slices in
+// all, an eighth of each slice's rows (the chip is not full otherwise); above,
+// whole slices (an XCD's L2 then serves all gathers of a slice), the next one
+// to the XCD with the fewest rows so far.
+void segment_tasks(const std::vector<const SegTable *> &tables, int nslices,
+                   std::vector<int2> &tasks, int &per) {
+  std::vector<int2> part[8];
+  const bool split = tables.size() * (size_t)nslices < 64;
+  size_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (size_t i = 0; i < tables.size(); ++i)
+    for (int s = 0; s < nslices; ++s) {
+      const SegTable &t = *tables[i];
+      const int who = (int)i | (s << 20);
+      if (split) {
+        for (int x = 0; x < 8; ++x)
+          for (int q = t.seg0[3][x]; q < t.seg0[3][x + 1]; ++q) part[x].push_back(make_int2(who, q));
+      } else {
+        int x = 0;
+        for (int y = 1; y < 8; ++y)
+          if (load[y] < load[x]) x = y;
+        load[x] += t.nseg;
+        for (int q = 0; q < t.nseg; ++q) part[x].push_back(make_int2(who, q));
+      }
+    }
+  size_t most = 0;
+  for (auto &p : part) most = std::max(most, p.size());
+  per = (int)most;
+  tasks.clear();
+  for (auto &p : part) {
+    p.resize(most, make_int2(0, -1));
+    tasks.insert(tasks.end(), p.begin(), p.end());
+  }
+}
+
 #define PF_SEG(T)                                                                              \
   template int segment_width<T>(int);                                                          \
   template void launch_segment<T>(hipStream_t, int, bool, int, const SegTable &, SegArgs<T>);  \
+  template void launch_segment_batch<T>(hipStream_t, int, bool, int, const SegItem<T> *,       \
+                                        const int2 *, int, const unsigned char *, long long,   \
+                                        long long);                                            \
   template void launch_to_slices<T>(hipStream_t, long long, int, const T *, long long, T *, T, \
                                     T *);                                                      \
   template void launch_from_slices<T>(hipStream_t, long long, int, const T *, T *, long long);

@@ -375,10 +375,12 @@ static void finish_filter_stats(polfed_ctx *ctx, double moved, double steps, dou
 // Whether the Clenshaw filters of n-row chains, cols columns in all, run in
 // one launch (resident.hip) rather than a launch a step.  Up to L = 14 always
 // (a step of L = 14, s = 8 FP64: 1.3 us against 5.0).  At L = 16 (FP32) a
-// column takes 7.5 us a step (13.5 with J2) on its compute unit, a launch
-// 5.2 us for 8 columns and 8.2 for 64 (10.7 with J2), so there only a batch
-// with more columns than that is better off.  A shape that asks for another
-// rank method than the tables keeps the step kernel.
+// column takes 7.5 us a step (13.5 with J2) on its compute unit whatever else
+// runs, a step by segments 3.5 us for 8 columns and up, so there only a batch
+// that fills half of the compute units is better off (filters of 32 members
+// of 8 columns, each to 20 eigenpairs: 0.41 s against 0.55; 256 members: 2.8
+// against 4.0).  A shape that asks for another rank method than the tables
+// keeps the step kernel.
 template <class T>
 static bool use_resident(const StepShape &shape, int form, long long n, long long cols) {
   const int f = resident_form(n, (int)sizeof(T));
@@ -1595,19 +1597,9 @@ int solve_one(polfed_ctx *ctx, const polfed_model *model, const polfed_opts *opt
 
 // Batched solve: realisations are grouped by block size and J2 != 0 (chain
 // lengths may mix); each group advances in lock step, one Lanczos block at a
-// time, with the filter of all its active members in one persistent launch
-// per Chebyshev step (k_step_batched), the K_max + 1 launches of a block
-// captured once in a HIP graph and replayed for every block.  Members whose
-// order K_i is below K_max idle for the first K_max - K_i steps; members
-// that converged are switched off in the device descriptor table.
-// Launch shape of the batched step kernel: the context's entry, else the
-// single-chain default with the tables as rank method and no column slices.
-static StepShape batch_shape_for(const polfed_ctx *ctx, int L, int S, bool fp32) {
-  auto it = ctx->batch_shapes.find(std::make_tuple(L, S, fp32 ? 4 : 8));
-  if (it != ctx->batch_shapes.end()) return it->second;
-  return default_batch_shape(L, S, fp32);
-}
-
+// time, with the filters of its active members in shared launches
+// (run_filter_batch): one for all steps of the short chains, one a step for
+// the others.
 // Algorithmic bytes of one realisation's batched Clenshaw filter (the byte
 // model of the single-chain filter: each streamed block once per step, the
 // state word and diagonal of every row where H~ is applied).
@@ -1623,60 +1615,127 @@ static double batched_filter_bytes(long long n, int S, long long K, const std::v
   return mv;
 }
 
-// Fill the chain fields and tile offsets of batch items (rows per tile rpi);
-// returns the launch's total tiles.
+// One member of a batched filter: its chain, blocks (buf: 3 n S values for the
+// recurrence) and filter.
 template <class T>
-static long long fill_batch_chains(std::vector<BatchItem<T>> &items,
-                                   const std::vector<const Chain *> &chains, long long rpi) {
-  long long tiles = 0;
-  for (size_t i = 0; i < items.size(); ++i) {
-    const Chain &c = *chains[i];
-    const Basis &b = *c.basis;
-    BatchItem<T> &it = items[i];
-    it.states = b.states.as<uint32_t>();
-    it.tabA = b.tabA.as<int32_t>();
-    it.tabB = b.tabB.as<uint16_t>();
-    it.n = b.n;
-    it.L = c.L;
-    it.half = b.half;
-    it.lomask = (1u << b.half) - 1u;
-    it.fullmask = (c.L >= 32) ? 0xffffffffu : ((1u << c.L) - 1u);
-    it.tile0 = tiles;
-    tiles += (b.n + rpi - 1) / rpi;
-  }
-  return tiles;
-}
+struct FilterMember {
+  const Chain *c;
+  const T *dt, *X;
+  T *Y, *buf;
+  long long ldx, ldy, K;
+  const double *coef;  // device
+  double c0, cK, Dinv;
+  T w1, w2, w1f, w2f;
+};
 
-// The distinct rank tables of a batched launch's chains, to be staged in
-// LDS (each item's tab set): at most kMaxBatchTables lengths, each L <=
-// kMaxLdsTableL, 96 KB in all; otherwise count = 0 and every realisation
-// reads its tables from global memory.
+// What a batched filter's launches read from the host: alive until they are
+// done.
 template <class T>
-static BatchTables batch_tables(std::vector<BatchItem<T>> &items,
-                                const std::vector<const Chain *> &chains) {
-  BatchTables bt;
-  std::memset(&bt, 0, sizeof(bt));
-  std::map<const Basis *, int> idx;
-  for (size_t i = 0; i < items.size(); ++i) {
-    const Basis *b = chains[i]->basis;
-    auto f = idx.find(b);
-    if (f == idx.end()) {
-      if (bt.count == kMaxBatchTables || chains[i]->L > kMaxLdsTableL) {
-        std::memset(&bt, 0, sizeof(bt));
-        return bt;
-      }
-      const int k = bt.count++;
-      bt.A[k] = b->tabA.as<int32_t>();
-      bt.B[k] = b->tabB.as<uint16_t>();
-      bt.half[k] = b->half;
-      bt.off[k] = bt.ints;
-      bt.ints += (1 << b->half) + (1 << b->half) / 2;
-      f = idx.emplace(b, k).first;
+struct FilterBatch {
+  std::vector<ResItem<T>> res;
+  std::vector<SegItem<T>> seg;
+  std::vector<int2> tasks;
+};
+
+// The Clenshaw filters of the members, S columns each and all of one bond set:
+// the short chains as resident launches, the others by segments, every step
+// one launch for all of them (all end together; a member of lower order idles
+// first).  Returns the steps of the longest.
+template <class T>
+static long long run_filter_batch(polfed_ctx *ctx, const std::vector<FilterMember<T>> &mem,
+                                  int S, bool has_j2, FilterBatch<T> &hold) {
+  hipStream_t st = ctx->stream;
+  std::map<int, long long> cols;  // columns of every chain length
+  for (auto &m : mem) cols[m.c->L] += S;
+  std::vector<std::pair<int, ResItem<T>>> res;
+  std::vector<const FilterMember<T> *> seg;
+  long long steps = 0;
+  const int w = segment_width<T>(S);
+  const bool sliced = w < S;
+  const uint32_t row = (uint32_t)(w * sizeof(T));
+  for (auto &m : mem) {
+    const long long n = m.c->basis->n;
+    steps = std::max(steps, m.K);
+    if (m.K == 0) {  // Y = c_0 X / D
+      StepArgs<T> a = base_args<T>(*m.c, m.dt);
+      a.out = m.Y;
+      a.ldo = m.ldy;
+      a.X = m.X;
+      a.ldx = m.ldx;
+      a.alpha = (T)(m.c0 * m.Dinv);
+      launch_step<T>(st, S, a, default_shape(m.c->L, S, sizeof(T) == 4), ctx->num_cu);
+    } else if (use_resident<T>(default_shape(m.c->L, S, sizeof(T) == 4), POLFED_FORM_CLENSHAW, n,
+                               cols[m.c->L])) {
+      ResItem<T> it = resident_item<T>(ctx, *m.c);
+      it.dt = m.dt;
+      it.X = m.X;
+      it.Y = m.Y;
+      it.ldx = m.ldx;
+      it.ldy = m.ldy;
+      it.coef = m.coef;
+      it.Dinv = m.Dinv;
+      it.w1 = m.w1;
+      it.w2 = m.w2;
+      it.w1f = m.w1f;
+      it.w2f = m.w2f;
+      it.K = m.K;
+      res.emplace_back(m.c->L, it);
+    } else {
+      seg.push_back(&m);
     }
-    items[i].taboff = bt.off[f->second];
   }
-  if ((size_t)bt.ints * sizeof(int32_t) > (size_t)96 * 1024) std::memset(&bt, 0, sizeof(bt));
-  return bt;
+  run_resident_batch<T>(ctx, res, hold.res, S, has_j2);
+  if (seg.empty()) return steps;
+  hold.seg.clear();
+  std::vector<const SegTable *> tables;
+  int Lmax = 0;
+  long long Kmax = 0;
+  for (const FilterMember<T> *m : seg) {
+    const long long n = m->c->basis->n;
+    const SegTable &t = ctx->seg_table(m->c->L);
+    tables.push_back(&t);
+    Lmax = std::max(Lmax, m->c->L);
+    Kmax = std::max(Kmax, m->K);
+    SegItem<T> it;
+    std::memset(&it, 0, sizeof(it));
+    it.rec = t.rec.as<int>();
+    it.dt = m->dt;
+    it.b0 = m->buf;
+    it.b1 = m->buf + (size_t)n * S;
+    T *xp = m->buf + (size_t)2 * n * S;
+    it.X = sliced ? xp : m->X;
+    it.xrow = sliced ? row : (uint32_t)(m->ldx * sizeof(T));
+    it.Y = m->Y;
+    it.orow = sliced ? 0 : (uint32_t)(m->ldy * sizeof(T));
+    it.ss = (size_t)n * row;
+    it.coef = m->coef;
+    it.Dinv = m->Dinv;
+    it.K = m->K;
+    it.w1 = m->w1;
+    it.w2 = m->w2;
+    it.w1f = m->w1f;
+    it.w2f = m->w2f;
+    hold.seg.push_back(it);
+    launch_to_slices<T>(st, n, S, m->X, m->ldx, sliced ? xp : nullptr, (T)m->cK, it.b0);
+  }
+  int per = 0;
+  segment_tasks(tables, S / w, hold.tasks, per);
+  SegItem<T> *items = static_cast<SegItem<T> *>(
+      ctx->buf("seg_items").ensure(sizeof(SegItem<T>) * hold.seg.size()));
+  int2 *tasks = static_cast<int2 *>(ctx->buf("seg_tasks").ensure(sizeof(int2) * hold.tasks.size()));
+  PF_HIP(hipMemcpyAsync(items, hold.seg.data(), sizeof(SegItem<T>) * hold.seg.size(),
+                        hipMemcpyHostToDevice, st));
+  PF_HIP(hipMemcpyAsync(tasks, hold.tasks.data(), sizeof(int2) * hold.tasks.size(),
+                        hipMemcpyHostToDevice, st));
+  const unsigned char *rows = tables[0]->rows.template as<unsigned char>();
+  for (long long j = 1; j <= Kmax; ++j)
+    launch_segment_batch<T>(st, Lmax, has_j2, S, items, tasks, per, rows, j, Kmax);
+  if (sliced)
+    for (size_t i = 0; i < seg.size(); ++i)
+      launch_from_slices<T>(st, seg[i]->c->basis->n, S,
+                            (seg[i]->K & 1) ? hold.seg[i].b1 : hold.seg[i].b0, seg[i]->Y,
+                            seg[i]->ldy);
+  return steps;
 }
 
 // The FP64 refinement filters UR = P^{K_r}(H~) Vn of the members `ids`
@@ -1698,57 +1757,7 @@ static void refine_batched(polfed_ctx *ctx, std::vector<std::unique_ptr<Realizat
   try {
     for (auto &ch : chunks) {
       const int c0 = ch.first.first, w = ch.first.second;
-      // members whose chains fit the resident filter, then the others
-      std::vector<int> all;
-      {
-        std::vector<int> res;
-        for (int i : ch.second)
-          (resident_form(rs[i]->n, (int)sizeof(double)) > 0 ? res : all).push_back(i);
-        size_t ncoef = 0, co = 0;
-        for (int i : res) ncoef += rs[i]->coef_r.size();
-        double *coefs = static_cast<double *>(
-            ctx->buf("res_coef").ensure(sizeof(double) * std::max<size_t>(1, ncoef)));
-        std::vector<std::pair<int, ResItem<double>>> mem;
-        double wsum = 0.0;
-        long long Kmax = 0;
-        for (int i : res) {
-          Realization<T> &r = *rs[i];
-          ResItem<double> it = resident_item<double>(ctx, r.c);
-          PF_HIP(hipMemcpyAsync(coefs + co, r.coef_r.data(), sizeof(double) * r.coef_r.size(),
-                                hipMemcpyHostToDevice, st));
-          it.dt = r.dt64b.template as<double>();
-          it.X = r.Vnb.template as<double>() + c0;
-          it.Y = r.URb.template as<double>() + c0;
-          it.ldx = it.ldy = r.ldr;
-          it.coef = coefs + co;
-          it.Dinv = 1.0 / r.D_r;
-          it.w1 = r.a * r.c.J1;
-          it.w2 = r.a * r.c.J2;
-          it.w1f = 0.5 * it.w1 * it.Dinv;
-          it.w2f = 0.5 * it.w2 * it.Dinv;
-          it.K = r.K_r;
-          co += r.coef_r.size();
-          wsum += (double)r.n * (r.K_r + 1);
-          Kmax = std::max(Kmax, r.K_r);
-          mem.emplace_back(r.c.L, it);
-        }
-        if (!mem.empty()) {
-          PF_HIP(hipEventRecord(e0, st));
-          std::vector<ResItem<double>> items;
-          run_resident_batch<double>(ctx, mem, items, w, rs[res[0]]->c.J2 != 0.0);
-          PF_HIP(hipEventRecord(e1, st));
-          PF_HIP(hipEventSynchronize(e1));
-          float ms = 0.0f;
-          PF_HIP(hipEventElapsedTime(&ms, e0, e1));
-          for (int i : res) {
-            Realization<T> &r = *rs[i];
-            const double f = (double)r.n * (r.K_r + 1) / wsum;
-            r.filter_gpu_s += 1e-3 * ms * f;
-            r.filter_launches += (double)(Kmax + 1) * f;
-            r.refine_bytes += batched_filter_bytes<double>(r.n, w, r.K_r, r.coef_r);
-          }
-        }
-      }
+      const std::vector<int> &all = ch.second;
       size_t k0 = 0;
       while (k0 < all.size()) {
         size_t k1 = k0, tot = 0;
@@ -1758,69 +1767,52 @@ static void refine_batched(polfed_ctx *ctx, std::vector<std::unique_ptr<Realizat
           tot += need;
           ++k1;
         }
-        const int B = (int)(k1 - k0);
         double *cheb = static_cast<double *>(ctx->buf("ref_cheb").ensure(tot));
         size_t ncoef = 0;
-        int Lmax = 0;
-        long long Kmax = 0;
-        for (size_t k = k0; k < k1; ++k) {
-          const Realization<T> &r = *rs[all[k]];
-          ncoef += r.coef_r.size();
-          Lmax = std::max(Lmax, r.c.L);
-          Kmax = std::max(Kmax, r.K_r);
-        }
+        for (size_t k = k0; k < k1; ++k) ncoef += rs[all[k]]->coef_r.size();
         double *coefs = static_cast<double *>(ctx->buf("ref_coef").ensure(sizeof(double) * ncoef));
-        std::vector<BatchItem<double>> items(B);
-        std::vector<const Chain *> chains(B);
+        std::vector<FilterMember<double>> mem;
+        FilterBatch<double> hold;
         size_t co = 0, bo = 0;
-        const Realization<T> *rmax_L = rs[all[k0]].get();
-        for (int k = 0; k < B; ++k) {
-          Realization<T> &r = *rs[all[k0 + k]];
-          if (r.c.L == Lmax) rmax_L = &r;
+        double wsum = 0.0;
+        for (size_t k = k0; k < k1; ++k) {
+          Realization<T> &r = *rs[all[k]];
           PF_HIP(hipMemcpyAsync(coefs + co, r.coef_r.data(), sizeof(double) * r.coef_r.size(),
                                 hipMemcpyHostToDevice, st));
-          BatchItem<double> &it = items[k];
-          std::memset(&it, 0, sizeof(it));
-          it.dt = r.dt64b.template as<double>();
-          it.X = r.Vnb.template as<double>() + c0;
-          it.ldx = r.ldr;
-          it.buf = cheb + bo;
-          it.Y = r.URb.template as<double>() + c0;
-          it.ldy = r.ldr;
-          it.coef = coefs + co;
-          it.Dinv = 1.0 / r.D_r;
-          it.w1 = r.a * r.c.J1;
-          it.w2 = r.a * r.c.J2;
-          it.K = r.K_r;
-          it.active = 1;
-          chains[k] = &r.c;
+          FilterMember<double> m;
+          m.c = &r.c;
+          m.dt = r.dt64b.template as<double>();
+          m.X = r.Vnb.template as<double>() + c0;
+          m.Y = r.URb.template as<double>() + c0;
+          m.ldx = m.ldy = r.ldr;
+          m.buf = cheb + bo;
+          m.coef = coefs + co;
+          m.K = r.K_r;
+          m.c0 = r.coef_r[0];
+          m.cK = r.coef_r[r.K_r];
+          m.Dinv = 1.0 / r.D_r;
+          m.w1 = r.a * r.c.J1;
+          m.w2 = r.a * r.c.J2;
+          m.w1f = 0.5 * m.w1 * m.Dinv;
+          m.w2f = 0.5 * m.w2 * m.Dinv;
+          mem.push_back(m);
           co += r.coef_r.size();
           bo += (size_t)3 * r.n * w;
+          wsum += (double)r.n * (r.K_r + 1);
         }
-        const StepShape shape = batch_shape_for(ctx, Lmax, w, false);
-        const long long total = fill_batch_chains(items, chains, batched_tile_rows<double>(w, shape));
-        const BatchTables bt = batch_tables(items, chains);
-        BatchItem<double> *itemsd = static_cast<BatchItem<double> *>(
-            ctx->buf("ref_items").ensure(sizeof(BatchItem<double>) * B));
-        PF_HIP(hipMemcpyAsync(itemsd, items.data(), sizeof(BatchItem<double>) * B,
-                              hipMemcpyHostToDevice, st));
-        StepArgs<double> base = base_args<double>(rmax_L->c, rmax_L->dt64b.template as<double>());
         PF_HIP(hipEventRecord(e0, st));
-        for (long long j = 0; j <= Kmax; ++j)
-          launch_step_batched<double>(st, w, base, itemsd, B, j, Kmax, total, bt, shape,
-                                      ctx->num_cu);
+        const long long Kmax =
+            run_filter_batch<double>(ctx, mem, w, rs[all[k0]]->c.J2 != 0.0, hold);
         PF_HIP(hipEventRecord(e1, st));
         PF_HIP(hipEventSynchronize(e1));
         float ms = 0.0f;
         PF_HIP(hipEventElapsedTime(&ms, e0, e1));
-        double wsum = 0.0;
-        for (int k = 0; k < B; ++k) wsum += (double)items[k].n * (items[k].K + 1);
         if (std::getenv("POLFED_VERBOSE"))
           fprintf(stderr, "[polfed] batched refinement filter: %d members, width %d, K_max %lld: "
-                          "%.2f s\n", B, w, Kmax, 1e-3 * ms);
-        for (int k = 0; k < B; ++k) {
-          Realization<T> &r = *rs[all[k0 + k]];
-          const double f = (double)items[k].n * (items[k].K + 1) / wsum;
+                          "%.2f s\n", (int)mem.size(), w, Kmax, 1e-3 * ms);
+        for (size_t k = k0; k < k1; ++k) {
+          Realization<T> &r = *rs[all[k]];
+          const double f = (double)r.n * (r.K_r + 1) / wsum;
           r.filter_gpu_s += 1e-3 * ms * f;
           r.filter_launches += (double)(Kmax + 1) * f;
           r.refine_bytes += batched_filter_bytes<double>(r.n, w, r.K_r, r.coef_r);
@@ -1894,148 +1886,64 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
       if (worst == POLFED_OK) worst = POLFED_NOT_CONVERGED;
       continue;
     }
-    // members whose filters run as resident launches, and those that share a
-    // launch a step; the longest chain of these names the launch shape
-    std::map<int, int> per_L;
-    for (auto &r : rs)
-      if (!r->err) ++per_L[r->c.L];
-    std::vector<int> resident, stepped;
-    for (int i = 0; i < B; ++i) {
-      if (rs[i]->err) continue;
-      const StepShape shb = batch_shape_for(ctx, rs[i]->c.L, rs[i]->s, rs[i]->fp32);
-      (use_resident<T>(shb, POLFED_FORM_CLENSHAW, rs[i]->n, (long long)per_L[rs[i]->c.L] * rs[i]->s)
-           ? resident
-           : stepped)
-          .push_back(i);
-    }
+    // recurrence buffers and coefficients of every member
     const int S = rs[first_ok]->s;
     const bool has_j2 = g.first.second != 0;
-    const int NS = (int)stepped.size();
-    int rL = stepped.empty() ? first_ok : stepped[0];
-    for (int i : stepped)
-      if (rs[i]->c.L > rs[rL]->c.L) rL = i;
-    const Realization<T> &r0 = *rs[rL];
-    // coefficients of every member; recurrence buffers and descriptors of the
-    // stepped ones
     size_t nbuf = 0, ncoef = 0;
-    long long Kmax = 0;  // of the stepped members
-    for (auto &r : rs) ncoef += r->coef.size();
-    for (int i : stepped) {
-      nbuf += (size_t)3 * rs[i]->n * S;
-      Kmax = std::max(Kmax, rs[i]->K);
+    for (auto &r : rs) {
+      if (r->err) continue;
+      nbuf += (size_t)3 * r->n * S;
+      ncoef += r->coef.size();
     }
-    DevBuf cheb, coefs, itemsd;
+    DevBuf cheb, coefs;
     cheb.ensure(sizeof(T) * nbuf);
     coefs.ensure(sizeof(double) * ncoef);
-    std::vector<const double *> coef_at(B);
+    std::vector<FilterMember<T>> members(B);
     size_t co = 0, bo = 0;
     for (int i = 0; i < B; ++i) {
       Realization<T> &r = *rs[i];
-      coef_at[i] = coefs.as<double>() + co;
+      if (r.err) continue;
       PF_HIP(hipMemcpyAsync(coefs.as<double>() + co, r.coef.data(), sizeof(double) * r.coef.size(),
                             hipMemcpyHostToDevice, st));
+      FilterMember<T> &m = members[i];
+      m.c = &r.c;
+      m.dt = r.dt();
+      m.X = r.Xs();
+      m.Y = r.Ys();
+      m.ldx = m.ldy = S;
+      m.buf = cheb.as<T>() + bo;
+      m.coef = coefs.as<double>() + co;
+      m.K = r.K;
+      m.c0 = r.coef[0];
+      m.cK = r.coef[r.K];
+      m.Dinv = 1.0 / r.D;
+      m.w1 = (T)(r.a * r.c.J1);
+      m.w2 = (T)(r.a * r.c.J2);
+      m.w1f = (T)(0.5 * (double)m.w1 * m.Dinv);
+      m.w2f = (T)(0.5 * (double)m.w2 * m.Dinv);
       co += r.coef.size();
-    }
-    std::vector<BatchItem<T>> items(NS);
-    std::vector<const Chain *> chains(NS);
-    for (int k = 0; k < NS; ++k) {
-      Realization<T> &r = *rs[stepped[k]];
-      BatchItem<T> &it = items[k];
-      std::memset(&it, 0, sizeof(it));
-      it.dt = r.dt();
-      it.X = r.Xs();
-      it.ldx = S;
-      it.buf = cheb.as<T>() + bo;
-      it.Y = r.Ys();
-      it.ldy = S;
-      it.coef = coef_at[stepped[k]];
-      it.Dinv = 1.0 / r.D;
-      it.w1 = (T)(r.a * r.c.J1);
-      it.w2 = (T)(r.a * r.c.J2);
-      it.K = r.K;
-      it.active = 1;
-      chains[k] = &r.c;
       bo += (size_t)3 * r.n * S;
     }
-    auto res_member = [&](int i) {
-      Realization<T> &r = *rs[i];
-      ResItem<T> it = resident_item<T>(ctx, r.c);
-      it.dt = r.dt();
-      it.X = r.Xs();
-      it.Y = r.Ys();
-      it.ldx = it.ldy = S;
-      it.coef = coef_at[i];
-      it.Dinv = 1.0 / r.D;
-      it.w1 = (T)(r.a * r.c.J1);
-      it.w2 = (T)(r.a * r.c.J2);
-      // (from the rounded weights, as the batched step kernel takes them)
-      it.w1f = (T)(0.5 * (double)it.w1 * it.Dinv);
-      it.w2f = (T)(0.5 * (double)it.w2 * it.Dinv);
-      it.K = r.K;
-      return std::make_pair(r.c.L, it);
-    };
-    const StepShape shape = batch_shape_for(ctx, r0.c.L, S, r0.fp32);
-    const long long total =
-        NS ? fill_batch_chains(items, chains, batched_tile_rows<T>(S, shape)) : 0;
-    const BatchTables bt = batch_tables(items, chains);
-    itemsd.ensure(sizeof(BatchItem<T>) * std::max(1, NS));
-    StepArgs<T> base = base_args<T>(r0.c, r0.dt());
-    hipGraphExec_t graph = nullptr;
     hipEvent_t e0, e1;
     PF_HIP(hipEventCreate(&e0));
     PF_HIP(hipEventCreate(&e1));
     double gfilter = 0.0, glaunch = 0.0;
     try {
       for (;;) {
-        int nact = 0, nstep = 0;
         std::vector<char> act(B, 0);  // members that take part in this block
+        std::vector<FilterMember<T>> now;
         for (int i = 0; i < B; ++i) {
           if (rs[i]->done) continue;
           act[i] = 1;
           rs[i]->filter_X();
-          ++nact;
+          now.push_back(members[i]);
         }
+        const int nact = (int)now.size();
         if (nact == 0) break;
-        for (int k = 0; k < NS; ++k) nstep += items[k].active = act[stepped[k]];
-        long long steps = nstep ? Kmax : 0;
-        std::vector<std::pair<int, ResItem<T>>> res;
-        std::vector<ResItem<T>> res_items;
-        for (int i : resident)
-          if (act[i]) {
-            res.push_back(res_member(i));
-            steps = std::max(steps, rs[i]->K);
-          }
-        if (nstep)
-          PF_HIP(hipMemcpyAsync(itemsd.p, items.data(), sizeof(BatchItem<T>) * NS,
-                                hipMemcpyHostToDevice, st));
-        if (nstep && !graph && ctx->use_graphs && Kmax <= (1LL << 17)) {
-          hipGraph_t gr = nullptr;
-          PF_HIP(hipStreamBeginCapture(ctx->own_stream, hipStreamCaptureModeThreadLocal));
-          try {
-            for (long long j = 0; j <= Kmax; ++j)
-              launch_step_batched<T>(ctx->own_stream, S, base, itemsd.as<BatchItem<T>>(), NS, j,
-                                     Kmax, total, bt, shape, ctx->num_cu);
-          } catch (...) {
-            hipGraph_t dummy = nullptr;
-            (void)hipStreamEndCapture(ctx->own_stream, &dummy);
-            if (dummy) (void)hipGraphDestroy(dummy);
-            throw;
-          }
-          PF_HIP(hipStreamEndCapture(ctx->own_stream, &gr));
-          hipError_t e = hipGraphInstantiate(&graph, gr, nullptr, nullptr, 0);
-          (void)hipGraphDestroy(gr);
-          PF_HIP(e);
-        }
         const double tf0 = now_s();
+        FilterBatch<T> hold;
         PF_HIP(hipEventRecord(e0, st));
-        run_resident_batch<T>(ctx, res, res_items, S, has_j2);
-        if (nstep && graph) {
-          PF_HIP(hipGraphLaunch(graph, st));
-        } else if (nstep) {
-          for (long long j = 0; j <= Kmax; ++j)
-            launch_step_batched<T>(st, S, base, itemsd.as<BatchItem<T>>(), NS, j, Kmax, total,
-                                   bt, shape, ctx->num_cu);
-        }
+        const long long steps = run_filter_batch<T>(ctx, now, S, has_j2, hold);
         PF_HIP(hipEventRecord(e1, st));
         PF_HIP(hipEventSynchronize(e1));
         float ms = 0.0f;
@@ -2090,12 +1998,10 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
         }
       }
     } catch (...) {
-      if (graph) (void)hipGraphExecDestroy(graph);
       (void)hipEventDestroy(e0);
       (void)hipEventDestroy(e1);
       throw;
     }
-    if (graph) PF_HIP(hipGraphExecDestroy(graph));
     PF_HIP(hipEventDestroy(e0));
     PF_HIP(hipEventDestroy(e1));
     cheb.release();

@@ -91,3 +91,22 @@ def test_moments_by_segments(ctx, pf, L, J2, nvec, nmom):
         ctx.set_step_shape(L, S, 0, *saved)
     assert mu[0] == 1.0
     assert np.abs(mu - ref).max() <= 1e-12
+
+
+# an eighth of every slice to an XCD, and whole slices (64 and more of them);
+# one slice a block (rows of X and Y used in place) and several
+@pytest.mark.parametrize("lengths,R,prec,s,J2", [((16, 18), 4, 1, 4, 0.0), ((16,), 17, 0, 8, 0.7),
+                                                 ((16, 14, 18), 5, 0, 2, 0.0)])
+def test_batch_by_segments_equals_single_solves(ctx, pf, lengths, R, prec, s, J2):
+    import numpy as np
+    from paper_2005_09534_amd import workloads
+    Ls = [lengths[r % len(lengths)] for r in range(R)]
+    models = [pf.make_model(L, 1.0, J2, 1.0, workloads.fields(L, 3.0, 70 + r))
+              for r, L in enumerate(Ls)]
+    kw = dict(precision=prec, block_size=s, target=0.1, window_factor=4.0)
+    b = ctx.solve_batch(models, 4, **kw)
+    for r in (0, R - 1):
+        one = ctx.solve(models[r], 4, vectors=False, **kw)
+        assert b["status"][r] == one["status"] == 0
+        # both within 1e-8 ||H|| in residual; eigenvalue errors are second order
+        assert np.abs(one["E"] - b["E"][r]).max() <= 1e-10 * one["info"]["normH"]
