@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace polfed {
 
@@ -28,129 +29,260 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ gram --
 //
-// Workgroup = 4 waves; it owns a 64 (columns of X) x 64 (columns of Y)
-// output tile and a contiguous chunk of rows.  Wave w owns output rows
-// [16w, 16w+16) of the tile, i.e. 1 x 4 MFMA tiles of 16 x 16.  One MFMA
-// step contracts 4 rows: lane l supplies A[i=l%16][k=l/16] = X[row0+k][ci]
-// and B[k=l/16][j=l%16] = Y[row0+k][cj]; the result tile holds
+// C = X^T Y on v_mfma_f64_16x16x4f64.  One MFMA step contracts 4 rows: lane l
+// supplies A[i=l%16][k=l/16] and B[k=l/16][j=l%16]; the result tile holds
 // D[l/16 + 4v][l%16] in component v of lane l (checked on gfx950).
+//
+// A wave owns 32 columns of X, as two tiles, the even and the odd ones, so
+// that one 16-byte load feeds both; likewise 32 columns of Y (NB = 2 tiles) or
+// 16 (NB = 1).  Of a workgroup's four waves, WM lie next to each other in X and
+// WN in Y, the others share the rows of the chunk (their tiles are added in
+// LDS); the next 8 rows are loaded while these are multiplied.  Bound by
+// reading X where q <= 32, by MFMA at q = 64.  With 64 x 64 tiles whatever q
+// was, 8-byte loads and chunks of at least 256 rows: n = 705,432, p = 480, q =
+// 32 1040 us, n = 3,432, p = 104, q = 8 a call of 32 us; so 650 (4.3 TB/s) and 21.  (Four
+// tiles of Y a wave, 64 registers of sums, spill.)
 
-constexpr int kGramTM = 64, kGramTN = 64;
+typedef double D2 __attribute__((ext_vector_type(2), aligned(8)));
 
-__global__ __launch_bounds__(256) void k_gram(long long n, int p, int q, const double *X,
-                                              long long ldx, const double *Y, long long ldy,
-                                              double *part, long long rows_per_chunk,
-                                              int tiles_m, int tiles_n) {
+// Two neighbouring elements of a row, zero past the last of `left`.
+__device__ __forceinline__ D2 pair_load(const double *p, int left) {
+  D2 v = {0.0, 0.0};
+  if (left >= 2)
+    v = *reinterpret_cast<const D2 *>(p);
+  else if (left == 1)
+    v[0] = p[0];
+  return v;
+}
+
+// One operand of a wave: its lanes' columns of a row-major matrix of `cols`
+// columns, as pairs (c, c + 1) or (PAIR false) singly.  Columns past the last
+// one are read from within the row instead (what they give goes to rows or
+// columns of the result that are not stored); of a pair that straddles the
+// end, the one before it is read and its second value taken.
+template <bool PAIR>
+struct GramSide {
+  const char *base;   // of the row that comes next (scalar)
+  long long step;     // bytes of four rows (scalar)
+  uint32_t off;       // this lane's bytes: its row of the four, its column
+  bool second;
+  __device__ __forceinline__ GramSide() {}
+  __device__ __forceinline__ GramSide(const double *M, long long ld, long long row, int cols,
+                                      int c, int kk) {
+    const int at = PAIR ? min(c, cols - 2) : min(c, cols - 1);
+    second = PAIR && c > at;
+    base = reinterpret_cast<const char *>(M + row * ld);
+    step = 32 * ld;
+    off = (uint32_t)(8 * (kk * ld + at));
+  }
+  __device__ __forceinline__ D2 fix(D2 v) const {
+    if (PAIR && second) v[0] = v[1];
+    return v;
+  }
+  __device__ __forceinline__ D2 at(const char *row, uint32_t lane) const {
+    D2 v;
+    if (PAIR)
+      v = *reinterpret_cast<const D2 *>(row + lane);
+    else
+      v[0] = v[1] = *reinterpret_cast<const double *>(row + lane);
+    return v;
+  }
+  // step s of the rows from here
+  __device__ __forceinline__ D2 get(int s) const { return at(base + s * step, off); }
+  // the last rows, `left` of the four: the others zero
+  __device__ __forceinline__ D2 tail(int kk, int left, long long ld) const {
+    D2 v = at(base, kk < left ? off : (uint32_t)(off - 8 * kk * ld));
+    if (kk >= left) v = (D2){0.0, 0.0};
+    return fix(v);
+  }
+};
+
+template <int NB, int WM, int WN, bool PX>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gram(
+    long long n, int p, int q, const double *X, long long ldx, const double *Y, long long ldy,
+    double *part, long long rows_per_chunk, int tiles_m, int tiles_n) {
+  constexpr int WK = 4 / (WM * WN);
+  constexpr int RS = 2;  // steps of four rows loaded at once
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
   int t = blockIdx.x;
   const int tm = t % tiles_m;
   t /= tiles_m;
   const int tn = t % tiles_n;
   const int chunk = t / tiles_n;
-  const long long r0 = (long long)chunk * rows_per_chunk;
-  long long r1 = r0 + rows_per_chunk;
-  if (r1 > n) r1 = n;
+  const long long c0 = (long long)chunk * rows_per_chunk;
+  const long long c1 = (c0 + rows_per_chunk < n) ? c0 + rows_per_chunk : n;
+  // this wave's rows of the chunk
+  const long long per = rows_per_chunk / WK;
+  const long long r0 = c0 + wk * per;
+  const long long r1 = (r0 + per < c1) ? r0 + per : c1;
+  const int i16 = lane & 15, kk = lane >> 4;
 
-  const int ci = tm * kGramTM + wave * 16 + (lane & 15);  // X column for A operand
-  const int kk = lane >> 4;                                // row within the 4-row step
-  const bool ci_ok = ci < p;
-  int cj[4];
-  bool cj_ok[4];
+  const int x0 = (tm * WM + wm) * 32, y0 = (tn * WN + wn) * 16 * NB;
+  d4 acc[2][NB];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    cj[u] = tn * kGramTN + u * 16 + (lane & 15);
-    cj_ok[u] = cj[u] < q;
-  }
-  d4 acc[4];
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int v = 0; v < NB; ++v) acc[u][v] = (d4){0.0, 0.0, 0.0, 0.0};
 
-  long long r = r0;
-  for (; r + 16 <= r1; r += 16) {
-    double av[4], bv[4][4];
+  if (x0 < p && y0 < q && r0 < r1) {
+    GramSide<PX> sx(X, ldx, r0, p, x0 + 2 * i16, kk);
+    GramSide<(NB > 1)> sy(Y, ldy, r0, q, y0 + (NB == 1 ? i16 : 2 * i16), kk);
+    struct Rows {
+      D2 a[RS], b[RS];
+    };
+    auto load = [&](Rows &w) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const long long row = r + 4 * s + kk;
-      av[s] = ci_ok ? X[row * ldx + ci] : 0.0;
+      for (int s = 0; s < RS; ++s) {
+        w.a[s] = sx.get(s);
+        w.b[s] = sy.get(s);
+      }
+      sx.base += RS * sx.step;
+      sy.base += RS * sy.step;
+    };
+    auto one = [&](D2 a, D2 b) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) bv[s][u] = cj_ok[u] ? Y[row * ldy + cj[u]] : 0.0;
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < NB; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
+    };
+    auto multiply = [&](const Rows &w) {
+#pragma unroll
+      for (int s = 0; s < RS; ++s) one(sx.fix(w.a[s]), sy.fix(w.b[s]));
+    };
+    long long left = (r1 - r0) / (4 * RS);  // whole loads
+    Rows cur, nxt;
+    if (left > 0) load(cur);
+    while (left > 0) {
+      if (left > 1) load(nxt);
+      multiply(cur);
+      if (left == 1) break;
+      if (left > 2) load(cur);
+      multiply(nxt);
+      left -= 2;
     }
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[s], bv[s][u], acc[u], 0, 0, 0);
-  }
-  for (; r < r1; r += 4) {
-    const long long row = r + kk;
-    const bool rok = row < r1;
-    const double a = (rok && ci_ok) ? X[row * ldx + ci] : 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const double bb = (rok && cj_ok[u]) ? Y[row * ldy + cj[u]] : 0.0;
-      acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bb, acc[u], 0, 0, 0);
+    for (int rem = (int)((r1 - r0) % (4 * RS)); rem > 0; rem -= 4) {
+      one(sx.tail(kk, rem, ldx), sy.tail(kk, rem, ldy));
+      sx.base += sx.step;
+      sy.base += sy.step;
     }
   }
-  // partial tile -> part[chunk][i][j] (p x q, row-major)
+  if constexpr (WK > 1) {  // the waves of one tile, in order
+    constexpr int W1 = WM * WN;
+    __shared__ d4 red[WK - 1][W1][2][NB][64];
+    const int at = wave % W1;
+    if (wk > 0)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < NB; ++v) red[wk - 1][at][u][v][lane] = acc[u][v];
+    __syncthreads();
+    if (wk > 0) return;
+#pragma unroll
+    for (int k = 0; k < WK - 1; ++k)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < NB; ++v) acc[u][v] += red[k][at][u][v][lane];
+  }
+  // partial tiles -> part[chunk][i][j] (p x q, row-major)
   double *out = part + (size_t)chunk * p * q;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = tn * kGramTN + u * 16 + (lane & 15);
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = tm * kGramTM + wave * 16 + (lane >> 4) + 4 * v;
-      if (i < p && j < q) out[(size_t)i * q + j] = acc[u][v];
+    for (int v = 0; v < NB; ++v) {
+      const int j = y0 + (NB == 1 ? i16 : 2 * i16 + v);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int i = x0 + 2 * (kk + 4 * c) + u;
+        if (i < p && j < q) out[(size_t)i * q + j] = acc[u][v][c];
+      }
     }
-  }
 }
 
-// C[i][j] = sum over chunks c of part[c][i][j]: one wavefront per output
-// element, lane l adding chunks l, l + 64, ... in order, then a fixed
-// butterfly over the lanes, so the result does not depend on timing.
+// C[i][j] = sum over chunks c of part[c][i][j]: a workgroup takes 16
+// neighbouring elements (a line of every partial tile) with 16 lanes each,
+// lane l adding chunks l, l + 16, ... in order, then the 16 lanes in order, so
+// the result does not depend on timing.
 __global__ __launch_bounds__(256) void k_gram_reduce(int p, int q, int nchunks,
                                                      const double *part, double *C,
                                                      long long ldc) {
-  const long long e = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (e >= (long long)p * q) return;
-  const size_t pq = (size_t)p * q;
+  __shared__ double red[16][17];
+  const int el = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const long long e = (long long)blockIdx.x * 16 + el;
+  const long long pq = (long long)p * q;
   double s = 0.0;
-  for (int c = lane; c < nchunks; c += 64) s += part[(size_t)c * pq + e];
+  if (e < pq) {
+#pragma unroll 8
+    for (int c = g; c < nchunks; c += 16) s += part[(size_t)c * pq + e];
+  }
+  red[g][el] = s;
+  __syncthreads();
+  if (g == 0 && e < pq) {
+    s = 0.0;
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
-  if (lane == 0) {
+    for (int k = 0; k < 16; ++k) s += red[k][el];
     const int i = (int)(e / q), j = (int)(e % q);
     C[(size_t)i * ldc + j] = s;
   }
 }
 
+// Tiles of the Gram product for a p x q output: a workgroup's waves along X
+// and along Y (two tiles of Y a wave, one for q <= 16).
+static void gram_tiles(int p, int q, int &wm, int &wn, int &tiles_m, int &tiles_n) {
+  wn = q <= 32 ? 1 : 2;
+  wm = p <= 32 ? 1 : (p <= 64 || wn == 2) ? 2 : 4;
+  tiles_m = (p + 32 * wm - 1) / (32 * wm);
+  tiles_n = (q + 32 * wn - 1) / (32 * wn);
+}
+
 // Row chunks of the Gram product for n rows and a p x q output: about four
-// workgroups per CU in all, at least 256 rows a chunk, and (cap > 0) no
-// more chunks than cap / (p q) partial tiles hold.
+// workgroups per CU in all, at least 64 rows a wave (four rounds of loads; n =
+// 3,432, p = 104, q = 8: a call of 21 us with 64, 32 with 256), and (cap > 0) no more
+// chunks than cap / (p q) partial tiles hold.
 long long gram_chunks(long long n, int p, int q, int num_cu, long long cap,
                       long long &rows_per_chunk) {
-  const int tiles_m = (p + kGramTM - 1) / kGramTM;
-  const int tiles_n = (q + kGramTN - 1) / kGramTN;
+  int wm, wn, tiles_m, tiles_n;
+  gram_tiles(p, q, wm, wn, tiles_m, tiles_n);
   long long want = std::max<long long>(1, (4LL * num_cu) / (tiles_m * tiles_n));
   if (cap > 0) want = std::min<long long>(want, cap / ((long long)p * q));
   want = std::max<long long>(want, 1);
-  rows_per_chunk = std::max<long long>(256, (n + want - 1) / want);
-  rows_per_chunk = ((rows_per_chunk + 15) / 16) * 16;
+  const int wk = 4 / (wm * wn);
+  rows_per_chunk = std::max<long long>(64 * wk, (n + want - 1) / want);
+  rows_per_chunk = ((rows_per_chunk + 16 * wk - 1) / (16 * wk)) * (16 * wk);
   return std::max<long long>(1, (n + rows_per_chunk - 1) / rows_per_chunk);
 }
 
 void launch_gram_parts(hipStream_t st, long long n, int p, int q, const double *X,
                        long long ldx, const double *Y, long long ldy, double *C, long long ldc,
                        double *part, long long rows_per_chunk, long long nchunks) {
-  const int tiles_m = (p + kGramTM - 1) / kGramTM;
-  const int tiles_n = (q + kGramTN - 1) / kGramTN;
-  const long long nblk = nchunks * tiles_m * tiles_n;
-  k_gram<<<(unsigned)nblk, 256, 0, st>>>(n, p, q, X, ldx, Y, ldy, part, rows_per_chunk, tiles_m,
-                                         tiles_n);
+  int wm, wn, tiles_m, tiles_n;
+  gram_tiles(p, q, wm, wn, tiles_m, tiles_n);
+  const unsigned nblk = (unsigned)(nchunks * tiles_m * tiles_n);
+  auto go = [&](auto kernel) {
+    kernel<<<nblk, 256, 0, st>>>(n, p, q, X, ldx, Y, ldy, part, rows_per_chunk, tiles_m, tiles_n);
+  };
+  if (q <= 16) {
+    if (p < 2)
+      go(k_gram<1, 1, 1, false>);
+    else
+      wm == 1 ? go(k_gram<1, 1, 1, true>) : wm == 2 ? go(k_gram<1, 2, 1, true>) : go(k_gram<1, 4, 1, true>);
+  } else if (wn == 1) {
+    if (p < 2)
+      go(k_gram<2, 1, 1, false>);
+    else
+      wm == 1 ? go(k_gram<2, 1, 1, true>) : wm == 2 ? go(k_gram<2, 2, 1, true>) : go(k_gram<2, 4, 1, true>);
+  } else {
+    if (p < 2)
+      go(k_gram<2, 1, 2, false>);
+    else
+      wm == 1 ? go(k_gram<2, 1, 2, true>) : go(k_gram<2, 2, 2, true>);
+  }
   check_launch("k_gram");
   const long long tot = (long long)p * q;
-  k_gram_reduce<<<(unsigned)((tot + 3) / 4), 256, 0, st>>>(p, q, (int)nchunks, part, C, ldc);
+  k_gram_reduce<<<(unsigned)((tot + 15) / 16), 256, 0, st>>>(p, q, (int)nchunks, part, C, ldc);
   check_launch("k_gram_reduce");
 }
 
@@ -166,49 +298,79 @@ void launch_gram(hipStream_t st, long long n, int p, int q, const double *X, lon
 
 // ---------------------------------------------------------------- update --
 //
-// Workgroup = 4 waves, 64 rows; wave w owns rows [16w, 16w+16) and all q
-// (<= 64) columns as up to 4 MFMA tiles.  Lane l supplies
-// A[i=l%16][k=l/16] = X[row0+i][k0+k] and B[k=l/16][j=l%16] = C[k0+k][j];
-// result component v of lane l is D[l/16 + 4v][l%16].
+// Y = alpha X C + beta Y.  A wave owns 16 rows and all q <= 64 columns (NB
+// tiles of 16); the sum over k goes in blocks of 64, whose rows of C are
+// staged in LDS once for the workgroup's NW waves (row stride = 16 mod 32
+// doubles: the four rows of an MFMA step in different banks).  Lane l = (i =
+// l%16, kk = l/16) reads X[row i][16 s + 4 kk .. + 3] of the block, so the four
+// lanes of a row take a whole 128-byte line between them, and the k of MFMA
+// step (s, e) is 16 s + 4 kk + e for both operands.  The next block's X is
+// loaded while this one's is multiplied.  Bound by reading X.  With 8-byte
+// loads of 4 k at a time and C from L1: n = 705,432, p = 480, q = 32 1235 us,
+// n = 3,432, p = 104, q = 8 a call of 21 us; so 752 (4.1 TB/s) and 18.
 
-__global__ __launch_bounds__(256) void k_update(long long n, int p, int q, double alpha,
-                                                const double *X, long long ldx, const double *C,
-                                                long long ldc, double beta, double *Y,
-                                                long long ldy) {
+// KU: k of a block (64; 32 and 16 where p is no more, so that short sums
+// stage and load no padding).
+template <int NB, int NW, int KU>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_update(
+    long long n, int p, int q, double alpha,
+                                                    const double *X, long long ldx,
+                                                    const double *C, long long ldc, double beta,
+                                                    double *Y, long long ldy) {
+  constexpr int kLd = NB == 1 ? 16 : (NB == 2 ? 48 : 80);
+  constexpr int W = 16 * NB;
+  constexpr int NS = KU / 16;
+  __shared__ double sc[KU * kLd];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const long long row0 = (long long)blockIdx.x * 64 + wave * 16;
-  const long long ra = row0 + (lane & 15);
-  const bool ra_ok = ra < n;
-  const int kk = lane >> 4;
-  const int ntile = (q + 15) / 16;
-  d4 acc[4];
+  const long long row0 = ((long long)blockIdx.x * NW + wave) * 16;
+  const int i16 = lane & 15, kk = lane >> 4;
+  const long long ra = row0 + i16;
+  const double *xr = X + (ra < n ? ra : 0) * ldx + 4 * kk;
+  d4 acc[NB];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) acc[u] = (d4){0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < p; k0 += 4) {
-    const int k = k0 + kk;
-    const bool k_ok = k < p;
-    const double a = (ra_ok && k_ok) ? X[ra * ldx + k] : 0.0;
+  for (int u = 0; u < NB; ++u) acc[u] = (d4){0.0, 0.0, 0.0, 0.0};
+  D2 a[NS][2];
+  auto load = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (u < ntile) {
-        const int j = u * 16 + (lane & 15);
-        const double b = (k_ok && j < q) ? C[(size_t)k * ldc + j] : 0.0;
-        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[u], 0, 0, 0);
-      }
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        a[s][h] = pair_load(xr + k0 + 16 * s + 2 * h, p - (k0 + 16 * s + 4 * kk + 2 * h));
+  };
+  load(0);
+  for (int k0 = 0; k0 < p; k0 += KU) {
+    if (k0 > 0) __syncthreads();
+    for (int e = threadIdx.x; e < KU * W; e += 64 * NW) {
+      const int k = e / W, j = e % W;
+      sc[k * kLd + j] = (k0 + k < p && j < q) ? C[(size_t)(k0 + k) * ldc + j] : 0.0;
     }
+    __syncthreads();
+    D2 b[NS][2];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      b[s][0] = a[s][0];
+      b[s][1] = a[s][1];
+    }
+    if (k0 + KU < p) load(k0 + KU);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+          acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+              b[s][e / 2][e % 2], sc[(16 * s + 4 * kk + e) * kLd + 16 * u + i16], acc[u], 0, 0, 0);
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    if (u < ntile) {
-      const int j = u * 16 + (lane & 15);
+  for (int u = 0; u < NB; ++u) {
+    const int j = u * 16 + i16;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const long long row = row0 + (lane >> 4) + 4 * v;
-        if (row < n && j < q) {
-          double *y = Y + row * ldy + j;
-          *y = (beta == 0.0) ? alpha * acc[u][v] : alpha * acc[u][v] + beta * (*y);
-        }
+    for (int v = 0; v < 4; ++v) {
+      const long long row = row0 + kk + 4 * v;
+      if (row < n && j < q) {
+        double *y = Y + row * ldy + j;
+        *y = (beta == 0.0) ? alpha * acc[u][v] : alpha * acc[u][v] + beta * (*y);
       }
     }
   }
@@ -224,8 +386,27 @@ void launch_update(hipStream_t st, long long n, int p, int q, double alpha, cons
     launch_update(st, n, 1, q, 0.0, X, ldx, C, ldc, beta, Y, ldy);
     return;
   }
-  k_update<<<(unsigned)((n + 63) / 64), 256, 0, st>>>(n, p, q, alpha, X, ldx, C, ldc, beta, Y,
-                                                      ldy);
+  // eight waves share a block of C where that still gives every CU work
+  const int nw = n >= 65536 ? 8 : 4;
+  const unsigned nwg = (unsigned)((n + 16 * nw - 1) / (16 * nw));
+  auto go = [&](auto kernel) {
+    kernel<<<nwg, 64 * nw, 0, st>>>(n, p, q, alpha, X, ldx, C, ldc, beta, Y, ldy);
+  };
+  auto with_nb = [&](auto nb_c) {
+    constexpr int NB = decltype(nb_c)::value;
+    if (p <= 16)
+      nw == 8 ? go(k_update<NB, 8, 16>) : go(k_update<NB, 4, 16>);
+    else if (p <= 32)
+      nw == 8 ? go(k_update<NB, 8, 32>) : go(k_update<NB, 4, 32>);
+    else
+      nw == 8 ? go(k_update<NB, 8, 64>) : go(k_update<NB, 4, 64>);
+  };
+  if (q <= 16)
+    with_nb(std::integral_constant<int, 1>{});
+  else if (q <= 32)
+    with_nb(std::integral_constant<int, 2>{});
+  else
+    with_nb(std::integral_constant<int, 4>{});
   check_launch("k_update");
 }
 
