@@ -1050,9 +1050,9 @@ __device__ double block_sum(double v, double *sh) {
   return r;
 }
 
-__device__ double sum_partials(const double *part, int nblk, double *sh) {
+__device__ double sum_partials(const double *part, int nblk, double *sh, int stride = 1) {
   double s = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x) s += part[b];
+  for (int b = threadIdx.x; b < nblk; b += blockDim.x) s += part[(size_t)b * stride];
   return block_sum(s, sh);
 }
 
@@ -1070,12 +1070,12 @@ __global__ __launch_bounds__(kRedThreads) void k_dot_partials(long long n, const
 __global__ __launch_bounds__(kRedThreads) void k_lanczos_update(long long n, double *w,
                                                                 const double *v,
                                                                 const double *vprev,
-                                                                const double *part, int nblk,
+                                                                const double *part, int npart, int stride,
                                                                 double *alpha,
                                                                 const double *beta_prev,
                                                                 double *part2) {
   __shared__ double sh[kRedThreads];
-  const double a = sum_partials(part, nblk, sh);
+  const double a = sum_partials(part, npart, sh, stride);
   const double b = (vprev != nullptr) ? beta_prev[0] : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) alpha[0] = a;
   double s = 0.0;
@@ -1110,10 +1110,10 @@ void launch_dot_partials(hipStream_t st, long long n, const double *x, const dou
 }
 
 void launch_lanczos_update(hipStream_t st, long long n, double *w, const double *v,
-                           const double *vprev, const double *part, int nblk, double *alpha,
-                           const double *beta_prev, double *part2) {
-  k_lanczos_update<<<nblk, kRedThreads, 0, st>>>(n, w, v, vprev, part, nblk, alpha, beta_prev,
-                                                 part2);
+                           const double *vprev, const double *part, int npart, int stride,
+                           int nblk, double *alpha, const double *beta_prev, double *part2) {
+  k_lanczos_update<<<nblk, kRedThreads, 0, st>>>(n, w, v, vprev, part, npart, stride, alpha,
+                                                 beta_prev, part2);
   check_launch("k_lanczos_update");
 }
 

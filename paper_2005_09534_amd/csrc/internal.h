@@ -217,6 +217,13 @@ template <class T>
 void launch_resident(hipStream_t st, const ResItem<T> &one, const ResItem<T> *items, int B,
                      int total_wg, long long Kmax, int L, bool has_j2);
 
+// The bounds Lanczos of one short chain (resident_form > 0) in one launch:
+// alpha[steps], beta[0 .. steps] (beta[0] = 0) on the device from the start
+// vector `start`; w1, w2 = J1/2, J2/2.
+void launch_resident_lanczos(hipStream_t st, const ResItem<double> &it, const double *diag,
+                             const double *start, int steps, double w1, double w2, double *alpha,
+                             double *beta, bool has_j2);
+
 // segment.hip: the step kernel of the longer chains, by segments (rows that
 // share their bits from kSegM up).
 constexpr int kSegM = 10;
@@ -378,8 +385,8 @@ void launch_symmetrize(hipStream_t st, int s, double *A, int lda);
 void launch_dot_partials(hipStream_t st, long long n, const double *x, const double *y,
                          double *part, int nblk);
 void launch_lanczos_update(hipStream_t st, long long n, double *w, const double *v,
-                           const double *vprev, const double *part, int nblk, double *alpha,
-                           const double *beta_prev, double *part2);
+                           const double *vprev, const double *part, int npart, int stride,
+                           int nblk, double *alpha, const double *beta_prev, double *part2);
 void launch_lanczos_normalize(hipStream_t st, long long n, const double *w, double *vnext,
                               const double *part2, int nblk, double *beta);
 

@@ -451,6 +451,107 @@ __global__ __launch_bounds__(1024) void k_resident_tiles(ResItem<T> one, const R
   }
 }
 
+// Single-vector Lanczos for the spectral bounds: w = H v_k, alpha_k = v_k . w,
+// w -= alpha_k v_k + beta_k v_{k-1}, beta_{k+1} = ||w||, v_{k+1} = w /
+// beta_{k+1}, v in LDS, the two sums over the workgroup in a fixed order.  A
+// step of four launches took 14.6 us at L = 12 and 15.8 at L = 14; so 2.6 and
+// 4.1 (the gathers, three barriers, a root and a division in a row).
+template <int R, int N, bool J2>
+__global__ __launch_bounds__(1024) void k_resident_lanczos(ResItem<double> it, const double *diag,
+                                                           const double *start, int steps,
+                                                           double w1c, double w2c, double *alpha,
+                                                           double *beta) {
+  extern __shared__ char s_res[];
+  __shared__ double red[2][16];
+  const int n = it.n;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+  constexpr bool kMany = R * N * (J2 ? 2 : 1) > 7;
+  constexpr int CH = kMany ? 2 : N;
+  double *v = reinterpret_cast<double *>(s_res);
+  int turn = 0;
+  // sum over the workgroup; the two buffers take turns, so one barrier does
+  auto total = [&](double x) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+    if (lane == 0) red[turn][wave] = x;
+    __syncthreads();
+    double s = 0.0;
+    for (int k = 0; k < nw; ++k) s += red[turn][k];
+    turn ^= 1;
+    return s;
+  };
+  uint32_t a1[R][N], a2[R][J2 ? N : 1];
+  int np1[R], np2[R], p[R];
+  double d[R], own[R], old[R];
+  double s = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int t = r * nw + wave;
+    p[r] = t * 64 + lane;
+    const ResTile ti = it.tiles[t < it.ntile ? t : 0];
+    np1[r] = __builtin_amdgcn_readfirstlane(t < it.ntile ? (int)ti.np1 : 0);
+    np2[r] = __builtin_amdgcn_readfirstlane(t < it.ntile ? (int)ti.np2 : 0);
+    const uint32_t *w = it.words + ti.off + lane;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      a1[r][q] = (q < np1[r]) ? w[q * 64] : 0u;
+      if (J2) a2[r][q] = (q < np2[r]) ? w[(np1[r] + q) * 64] : 0u;
+    }
+    d[r] = own[r] = old[r] = 0.0;
+    if (p[r] < n) {
+      const int row = it.perm[p[r]];
+      d[r] = diag[row];
+      own[r] = start[row];
+      s += own[r] * own[r];
+    }
+  }
+  const double norm = sqrt(total(s));
+  const double inv0 = (norm > 1e-300) ? 1.0 / norm : 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    own[r] *= inv0;
+    if (p[r] < n) v[p[r]] = own[r];
+  }
+  if (threadIdx.x == 0) {
+    v[n] = 0.0;  // the slot that holds zero
+    beta[0] = 0.0;
+  }
+  __syncthreads();
+  double b = 0.0;
+  for (int k = 0; k < steps; ++k) {
+    double w[R], t = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      double acc = d[r] * own[r];
+      res_gather<double, CH, kMany>(a1[r], np1[r], s_res, w1c, acc);
+      if constexpr (J2) res_gather<double, CH, kMany>(a2[r], np2[r], s_res, w2c, acc);
+      w[r] = acc;
+      t += own[r] * acc;  // (rows past the end hold zero)
+    }
+    const double a = total(t);
+    t = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      w[r] = w[r] - a * own[r] - b * old[r];
+      t += w[r] * w[r];
+    }
+    b = sqrt(total(t));  // (every gather of v is done: two barriers since)
+    if (threadIdx.x == 0) {
+      alpha[k] = a;
+      beta[k + 1] = b;
+    }
+    const double inv = (b > 1e-300) ? 1.0 / b : 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      old[r] = own[r];
+      own[r] = w[r] * inv;
+      if (p[r] < n) v[p[r]] = own[r];
+    }
+    __syncthreads();
+  }
+}
+
 // ------------------------------------------------------------ launcher --
 
 // Rows a thread owns (1, 2 or 4), 0 for the tile form, -1 where the chain
@@ -502,6 +603,28 @@ void launch_resident(hipStream_t st, const ResItem<T> &one, const ResItem<T> *it
   } else {
     throw Error(POLFED_EINVAL, "resident filter: chain too long");
   }
+}
+
+void launch_resident_lanczos(hipStream_t st, const ResItem<double> &it, const double *diag,
+                             const double *start, int steps, double w1, double w2, double *alpha,
+                             double *beta, bool has_j2) {
+  const int form = resident_form(it.n, (int)sizeof(double));
+  const size_t shm = sizeof(double) * ((size_t)it.n + 1);
+  auto run = [&](auto kernel, int waves) {
+    kernel<<<1, 64 * waves, shm, st>>>(it, diag, start, steps, w1, w2, alpha, beta);
+  };
+  if (form == 1)
+    has_j2 ? run(k_resident_lanczos<1, 7, true>, it.ntile)
+           : run(k_resident_lanczos<1, 7, false>, it.ntile);
+  else if (form == 2)
+    has_j2 ? run(k_resident_lanczos<2, 7, true>, (it.ntile + 1) / 2)
+           : run(k_resident_lanczos<2, 7, false>, (it.ntile + 1) / 2);
+  else if (form == 4)
+    has_j2 ? run(k_resident_lanczos<4, 7, true>, (it.ntile + 3) / 4)
+           : run(k_resident_lanczos<4, 7, false>, (it.ntile + 3) / 4);
+  else
+    throw Error(POLFED_EINVAL, "resident Lanczos: chain too long");
+  check_launch("k_resident_lanczos");
 }
 
 template void launch_resident<float>(hipStream_t, const ResItem<float> &, const ResItem<float> *,

@@ -103,30 +103,6 @@ static StepShape shape_for(const polfed_ctx *ctx, int L, int S, bool fp32) {
   return default_shape(L, S, fp32);
 }
 
-// out = scale * (dt .* V + sum w_l V[nbr]) for a block of `width` columns,
-// split into power-of-two chunks of at most 64 columns.
-template <class T>
-static void apply_op(polfed_ctx *ctx, const Chain &c, const T *dt, double wscale1,
-                     double wscale2, const T *V, long long ldv, T *out, long long ldo, int width,
-                     bool fp32) {
-  int off = 0;
-  while (off < width) {
-    int S = 64;
-    while (S > width - off) S >>= 1;
-    attach_pattern(ctx, c, shape_for(ctx, c.L, S, fp32));
-    StepArgs<T> a = base_args<T>(c, dt);
-    a.V = V + off;
-    a.ldv = ldv;
-    a.out = out + off;
-    a.ldo = ldo;
-    a.dscale = T(1);
-    a.w1 = (T)wscale1;
-    a.w2 = (T)wscale2;
-    launch_step<T>(ctx->stream, S, a, shape_for(ctx, c.L, S, fp32), ctx->num_cu);
-    off += S;
-  }
-}
-
 // Y = P^K_sigma(H~) X = (sum_k c_k T_k(H~) X) / D by the forward three-term
 // recurrence: t_0 = X, t_1 = H~ X, t_{k+1} = 2 H~ t_k - t_{k-1}, each t_k
 // added to Y with weight c_k / D as it is made (steps after the last
@@ -306,6 +282,57 @@ static double queue_filter(hipStream_t stream, int num_cu, const StepShape &shap
 // method than the tables.
 static bool use_segments(const StepShape &shape, int L) {
   return shape.rank_incr == 0 && L >= kSegM + 4;
+}
+
+// out = scale * (dt .* V + sum w_l V[nbr]) for a block of `width` columns,
+// split into power-of-two chunks of at most 64 columns.  A block of one slice
+// goes by segments in place (one FP64 column: L = 16 25 us a call against 30,
+// L = 24 109 against 160); wider ones would have to be packed and unpacked for
+// the one product (L = 22, 64 FP64 columns: 687 us against 536) and take the
+// step kernel's tables, J1-J2 FP64 blocks beyond the Infinity Cache in four
+// column slices over the XCDs (64 FP64 columns, L = 22: 872 us against 967,
+// L = 24: 3.82 ms against 4.17; without J2 625 against 540, FP32 and smaller
+// blocks slower as well).
+template <class T>
+static void apply_op(polfed_ctx *ctx, const Chain &c, const T *dt, double wscale1,
+                     double wscale2, const T *V, long long ldv, T *out, long long ldo, int width,
+                     bool fp32) {
+  const long long n = c.basis->n;
+  int off = 0;
+  while (off < width) {
+    int S = 64;
+    while (S > width - off) S >>= 1;
+    const StepShape shape = shape_for(ctx, c.L, S, fp32);
+    if (use_segments(shape, c.L) && segment_width<T>(S) == S && ldv == S) {
+      SegArgs<T> a;
+      std::memset(&a, 0, sizeof(a));
+      a.dt = dt;
+      a.V = V + off;
+      a.out = out + off;
+      a.orow = (uint32_t)(ldo * sizeof(T));
+      a.dscale = T(1);
+      a.w1 = (T)wscale1;
+      a.w2 = (T)wscale2;
+      launch_segment<T>(ctx->stream, c.L, c.J2 != 0.0, S, ctx->seg_table(c.L), a);
+      off += S;
+      continue;
+    }
+    attach_pattern(ctx, c, shape);
+    StepArgs<T> a = base_args<T>(c, dt);
+    a.V = V + off;
+    a.ldv = ldv;
+    a.out = out + off;
+    a.ldo = ldo;
+    a.dscale = T(1);
+    a.w1 = (T)wscale1;
+    a.w2 = (T)wscale2;
+    if (sizeof(T) == 8 && S == 64 && c.J2 != 0.0 && (double)n * 512.0 > 256e6) {
+      a.nslices = 4;
+      a.vss = a.oss = S / 4;
+    }
+    launch_step<T>(ctx->stream, S, a, shape, ctx->num_cu);
+    off += S;
+  }
 }
 
 // The Clenshaw filter by segments, K >= 1.  buf3 holds b_{k+1} and b_{k+2} =
@@ -601,12 +628,39 @@ void make_chain(polfed_ctx *ctx, const polfed_model *m, Chain &c) {
 
 // ------------------------------------------------------------ bounds --
 
+// The extremes and residual bounds of the tridiagonal matrix of a Lanczos run.
+static void read_bounds(hipStream_t st, int steps, const double *alpha, const double *beta,
+                        double &E0, double &E1, double &r0, double &r1) {
+  std::vector<double> ha(steps), hb(steps + 1);
+  PF_HIP(hipMemcpyAsync(ha.data(), alpha, sizeof(double) * steps, hipMemcpyDeviceToHost, st));
+  PF_HIP(hipMemcpyAsync(hb.data(), beta, sizeof(double) * (steps + 1), hipMemcpyDeviceToHost, st));
+  PF_HIP(hipStreamSynchronize(st));
+  std::vector<double> off(steps, 0.0);
+  for (int k = 1; k < steps; ++k) off[k] = hb[k];
+  double ylo, yhi;
+  tridiag_extremes(ha, off, E0, E1, ylo, yhi);
+  r0 = std::fabs(hb[steps] * ylo);
+  r1 = std::fabs(hb[steps] * yhi);
+}
+
 void run_bounds(polfed_ctx *ctx, const Chain &c, int steps, unsigned long long seed, double &E0,
                 double &E1, double &r0, double &r1) {
   const long long n = c.basis->n;
   steps = (int)std::min<long long>(steps, n - 1);
   if (steps < 1) steps = 1;
   hipStream_t st = ctx->stream;
+  const int form = resident_form(n, (int)sizeof(double));
+  if (form > 0 && shape_for(ctx, c.L, 1, false).rank_incr == 0) {
+    // a short chain: the whole Lanczos run in one launch
+    double *sc = static_cast<double *>(
+        ctx->buf("bnd_scal").ensure(sizeof(double) * (2 * (size_t)steps + 1 + n)));
+    double *alpha = sc, *beta = sc + steps, *start = sc + 2 * steps + 1;
+    launch_philox_fill(st, n, 1, start, 1, seed, 0x5eedu);
+    launch_resident_lanczos(st, resident_item<double>(ctx, c), c.diag.as<double>(), start, steps,
+                            0.5 * c.J1, 0.5 * c.J2, alpha, beta, c.J2 != 0.0);
+    read_bounds(st, steps, alpha, beta, E0, E1, r0, r1);
+    return;
+  }
   double *vec = static_cast<double *>(ctx->buf("bnd_vec").ensure(sizeof(double) * 4 * n));
   double *v[3] = {vec, vec + n, vec + 2 * n};
   double *w = vec + 3 * n;
@@ -622,34 +676,47 @@ void run_bounds(polfed_ctx *ctx, const Chain &c, int steps, unsigned long long s
   launch_dot_partials(st, n, v[0], v[0], part2, nblk);
   launch_lanczos_normalize(st, n, v[0], v[0], part2, nblk, beta + steps);  // scratch beta slot
   launch_fill(st, beta, 1, 0.0);
-  attach_pattern(ctx, c, shape_for(ctx, c.L, 1, false));
+  const StepShape shape = shape_for(ctx, c.L, 1, false);
+  const bool seg = use_segments(shape, c.L);
+  const SegTable *table = seg ? &ctx->seg_table(c.L) : nullptr;
+  double *sums = seg ? static_cast<double *>(ctx->buf("bnd_sums").ensure(
+                           sizeof(double) * 2 * (size_t)table->nseg))
+                     : nullptr;
+  if (!seg) attach_pattern(ctx, c, shape);
   for (int k = 0; k < steps; ++k) {
     double *vk = v[k % 3];
     double *vprev = (k >= 1) ? v[(k + 2) % 3] : nullptr;
     double *vnext = v[(k + 1) % 3];
-    StepArgs<double> a = base_args<double>(c, c.diag.as<double>());
-    a.V = vk;
-    a.ldv = 1;
-    a.out = w;
-    a.ldo = 1;
-    a.dscale = 1.0;
-    a.w1 = 0.5 * c.J1;
-    a.w2 = 0.5 * c.J2;
-    launch_step<double>(st, 1, a, shape_for(ctx, c.L, 1, false), ctx->num_cu);
-    launch_dot_partials(st, n, vk, w, part, nblk);
-    launch_lanczos_update(st, n, w, vk, vprev, part, nblk, alpha + k, beta + k, part2);
+    if (seg) {  // w = H v_k, its segments leaving their sums of v_k . w
+      SegArgs<double> a;
+      std::memset(&a, 0, sizeof(a));
+      a.dt = c.diag.as<double>();
+      a.V = vk;
+      a.out = w;
+      a.orow = (uint32_t)sizeof(double);
+      a.dscale = 1.0;
+      a.w1 = 0.5 * c.J1;
+      a.w2 = 0.5 * c.J2;
+      a.dots = sums;
+      launch_segment<double>(st, c.L, c.J2 != 0.0, 1, *table, a);
+      launch_lanczos_update(st, n, w, vk, vprev, sums + 1, table->nseg, 2, nblk, alpha + k,
+                            beta + k, part2);
+    } else {
+      StepArgs<double> a = base_args<double>(c, c.diag.as<double>());
+      a.V = vk;
+      a.ldv = 1;
+      a.out = w;
+      a.ldo = 1;
+      a.dscale = 1.0;
+      a.w1 = 0.5 * c.J1;
+      a.w2 = 0.5 * c.J2;
+      launch_step<double>(st, 1, a, shape, ctx->num_cu);
+      launch_dot_partials(st, n, vk, w, part, nblk);
+      launch_lanczos_update(st, n, w, vk, vprev, part, nblk, 1, nblk, alpha + k, beta + k, part2);
+    }
     launch_lanczos_normalize(st, n, w, vnext, part2, nblk, beta + k + 1);
   }
-  std::vector<double> ha(steps), hb(steps + 1);
-  PF_HIP(hipMemcpyAsync(ha.data(), alpha, sizeof(double) * steps, hipMemcpyDeviceToHost, st));
-  PF_HIP(hipMemcpyAsync(hb.data(), beta, sizeof(double) * (steps + 1), hipMemcpyDeviceToHost, st));
-  PF_HIP(hipStreamSynchronize(st));
-  std::vector<double> off(steps, 0.0);
-  for (int k = 1; k < steps; ++k) off[k] = hb[k];
-  double ylo, yhi;
-  tridiag_extremes(ha, off, E0, E1, ylo, yhi);
-  r0 = std::fabs(hb[steps] * ylo);
-  r1 = std::fabs(hb[steps] * yhi);
+  read_bounds(st, steps, alpha, beta, E0, E1, r0, r1);
 }
 
 // ------------------------------------------------------------- the solve --
