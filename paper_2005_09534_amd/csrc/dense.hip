@@ -600,36 +600,45 @@ __global__ __launch_bounds__(256) void k_jacobi_round(int n, int r, const double
   }
 }
 
-// Batched cyclic Jacobi for many small symmetric matrices of one size: one
-// workgroup per matrix with the matrix (and, up to kLdsVecMax, the vectors) in
-// LDS.  The rotations, the 2 x 2 block updates and the stopping rule are those
-// of sym_eig, applied to each matrix on its own, so that many Lanczos
-// convergence checks of one batch run in a single launch.
-template <bool VLDS>
-__global__ __launch_bounds__(kEigThreads) void k_jacobi_lds(int n, double *A, double *V, double *w,
-                                                            double *Vout, int max_sweeps) {
-  extern __shared__ double sA[];  // m * ld, kEigRed for reductions, then V (VLDS)
+// Batched cyclic Jacobi for many small symmetric matrices of one size, so that
+// many Lanczos convergence checks of one batch run in a single launch.  The
+// rotations, the 2 x 2 block updates and the stopping rule are those of
+// sym_eig, applied to each matrix on its own: one workgroup per matrix turns
+// the matrix in LDS and leaves a log of its rotations, and a second launch
+// turns the rows of V, which need nothing of each other, over the whole chip
+// (16 us for n = 40, 31 for n = 80).  One matrix from scratch (us): n = 33 162,
+// n = 64 429, n = 96 1016, n = 128 2098; with V turned in LDS (n <= 96) or
+// global memory in each round, by the one workgroup, 190, 612, 1602 and 6237.
+// Latency bounds it: about 0.8 us a round of two barriers, LDS loads, two
+// reciprocal square roots one after the other and LDS stores.
+struct EigLog {
+  int rounds;
+  int rank[kLdsEigMax];  // of each index's eigenvalue
+};
+
+template <int NM>
+__global__ __launch_bounds__(kEigThreads) void k_jacobi_lds(int n, const double *A, double *w,
+                                                            EigLog *info, double2 *log,
+                                                            size_t log_per) {
+  extern __shared__ double sA[];  // m * ld, kEigRed for sums
   __shared__ JacobiRot rot;
   const int m = eig_even(n), ld = eig_ld(n);
   double *red = sA + (size_t)m * ld;
-  double *sV = red + kEigRed;
   const int t = threadIdx.x, nt = blockDim.x;
-  const size_t nn = (size_t)n * n;
-  double *Ab = A + (size_t)blockIdx.x * nn;
-  double *Vb = V + (size_t)blockIdx.x * nn;
+  const double *Ab = A + (size_t)blockIdx.x * n * n;
   for (int e = t; e < m * m; e += nt) {
     const int i = e / m, j = e % m;
     const bool in = i < n && j < n;
     sA[i * ld + j] = in ? Ab[(size_t)i * n + j] : 0.0;
-    if (VLDS && i < n) sV[i * ld + j] = in ? Vb[(size_t)i * n + j] : 0.0;
   }
   __syncthreads();
-  jacobi_sweeps<VLDS ? kVecLds : kVecGlobal>(n, sA, VLDS ? sV : Vb, red, rot, max_sweeps);
+  const int rounds =
+      jacobi_sweeps<NM, true>(n, sA, red, rot, kEigSweeps, log + blockIdx.x * log_per);
   __syncthreads();
-  // eigenvalues ascending (ties by index) and the matching columns of V
+  // eigenvalues ascending (ties by index)
   double *wb = w + (size_t)blockIdx.x * n;
-  double *Vo = Vout + (size_t)blockIdx.x * nn;
-  int *rank_of = reinterpret_cast<int *>(red);
+  EigLog &out = info[blockIdx.x];
+  if (t == 0) out.rounds = rounds;
   for (int i = t; i < n; i += nt) {
     const double di = sA[i * ld + i];
     int rank = 0;
@@ -638,33 +647,105 @@ __global__ __launch_bounds__(kEigThreads) void k_jacobi_lds(int n, double *A, do
       rank += (dj < di || (dj == di && j < i)) ? 1 : 0;
     }
     wb[rank] = di;
-    rank_of[i] = rank;
-  }
-  __syncthreads();
-  for (size_t e = t; e < nn; e += nt) {
-    const int row = (int)(e / n), i = (int)(e % n);
-    Vo[(size_t)row * n + rank_of[i]] = VLDS ? sV[row * ld + i] : Vb[e];
+    out.rank[i] = rank;
   }
 }
 
-bool sym_eig_batched(hipStream_t st, int n, int B, double *A, double *V, double *w,
-                     double *Vout) {
+// A lane's neighbour's value: lane + 1's or lane - 1's.
+template <int CTRL>
+__device__ __forceinline__ double wave_shift(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// Vout = V times the logged rotations, columns by rank; V null: the identity.
+// One wave holds kRows rows in its lanes, a lane the columns at positions k and
+// m - 1 - k of its row (indices k and m - 1 - k in round 0 and again after
+// every sweep); from one round to the next a column moves on by one position,
+// which is a shift of the lanes.  kAhead rounds of (c, s) are on their way.
+template <int NM>
+__global__ __launch_bounds__(64) void k_jacobi_rows(int n, const double *V, const EigLog *info,
+                                                    const double2 *log, size_t log_per,
+                                                    double *Vout) {
+  constexpr int kLanes = NM / 2, kRows = 64 / kLanes, kAhead = 16;
+  const int m = eig_even(n), npair = m / 2;
+  const int k = threadIdx.x & (kLanes - 1);
+  const int row = blockIdx.x * kRows + (int)threadIdx.x / kLanes;
+  const EigLog &in = info[blockIdx.y];
+  const size_t nn = (size_t)n * n;
+  const double *Vb = V ? V + blockIdx.y * nn : nullptr;
+  const bool holds = k < npair && row < n;
+  const int cb = m - 1 - k;
+  double top = 0.0, bot = 0.0;
+  if (holds) {
+    top = Vb ? Vb[(size_t)row * n + k] : (row == k) ? 1.0 : 0.0;
+    if (cb < n) bot = Vb ? Vb[(size_t)row * n + cb] : (row == cb) ? 1.0 : 0.0;
+  }
+  // (a lane without a pair reads the last pair's; nothing takes its values)
+  const double2 *lg = log + blockIdx.y * log_per + (k < npair ? k : npair - 1);
+  const int rounds = in.rounds;
+  const bool first = k == 0, last = k == npair - 1;
+  auto turn = [&](double2 x) {
+    const double p = x.x * top - x.y * bot, q = x.y * top + x.x * bot;
+    const double pn = wave_shift<0x130>(p), qp = wave_shift<0x138>(q);
+    top = first ? p : last ? q : pn;
+    bot = !first ? qp : (npair > 1) ? pn : q;
+  };
+  double2 cs[kAhead];
+  if (rounds >= kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) cs[u] = lg[(size_t)u * npair];
+  }
+  int r = 0;
+  for (; r + kAhead <= rounds; r += kAhead) {
+    // (past the end: the last round's, not used)
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const double2 x = cs[u];
+      cs[u] = lg[(size_t)std::min(r + u + kAhead, rounds - 1) * npair];
+      turn(x);
+    }
+  }
+  for (; r < rounds; ++r) turn(lg[(size_t)r * npair]);
+  if (!holds) return;
+  double *Vo = Vout + blockIdx.y * nn + (size_t)row * n;
+  Vo[in.rank[k]] = top;
+  if (cb < n) Vo[in.rank[cb]] = bot;
+}
+
+bool sym_eig_batched(hipStream_t st, int n, int B, const double *A, const double *V, double *w,
+                     double *Vout, DevBuf &log) {
   if (n < 1 || n > kLdsEigMax || B < 1) return false;
-  const bool vlds = n <= kLdsVecMax;
-  const size_t one = (size_t)eig_even(n) * eig_ld(n);
-  const size_t shm = sizeof(double) * (one * (vlds ? 2 : 1) + kEigRed);
-  const void *kernel = vlds ? reinterpret_cast<const void *>(k_jacobi_lds<true>)
-                            : reinterpret_cast<const void *>(k_jacobi_lds<false>);
-  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) !=
-      hipSuccess) {
+  const int m = eig_even(n);
+  const size_t shm = sizeof(double) * ((size_t)m * eig_ld(n) + kEigRed);
+  auto turn = n <= 64 ? k_jacobi_lds<64> : k_jacobi_lds<128>;
+  auto rows = n <= 64 ? k_jacobi_rows<64> : k_jacobi_rows<128>;
+  const int per_wave = n <= 64 ? 2 : 1;
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(turn),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  if (vlds)
-    k_jacobi_lds<true><<<B, kEigThreads, shm, st>>>(n, A, V, w, Vout, 40);
-  else
-    k_jacobi_lds<false><<<B, kEigThreads, shm, st>>>(n, A, V, w, Vout, 40);
-  check_launch("k_jacobi_lds");
+  // the log of all sweeps there may be, 5.2 MB a matrix for n > 64 and 1.3 up
+  // to there (one size each, so that growing matrices do not allocate anew),
+  // at most 166 MB at a time
+  const int mm = n <= 64 ? 64 : kLdsEigMax;
+  const size_t log_per = (size_t)(mm / 2) * (mm - 1) * kEigSweeps;
+  const int chunk = std::min(B, 32);
+  const size_t nn = (size_t)n * n;
+  EigLog *info = static_cast<EigLog *>(
+      log.ensure(chunk * (sizeof(EigLog) + 16 + sizeof(double2) * log_per)));
+  double2 *lg = reinterpret_cast<double2 *>(
+      reinterpret_cast<char *>(info) + ((chunk * sizeof(EigLog) + 15) & ~(size_t)15));
+  for (int b = 0; b < B; b += chunk) {
+    const int nb = std::min(chunk, B - b);
+    turn<<<nb, kEigThreads, shm, st>>>(n, A + b * nn, w + (size_t)b * n, info, lg, log_per);
+    check_launch("k_jacobi_lds");
+    rows<<<dim3((n + per_wave - 1) / per_wave, nb), 64, 0, st>>>(
+        n, V ? V + b * nn : nullptr, info, lg, log_per, Vout + b * nn);
+    check_launch("k_jacobi_rows");
+  }
   return true;
 }
 
@@ -734,6 +815,9 @@ void sym_eig(hipStream_t st, int n, double *A, double *w, double *V, DevBuf &wor
   if (n <= 0) return;
   if (n > 4096) throw Error(POLFED_EINVAL, "sym_eig: n must be <= 4096");
   const size_t nn = (size_t)n * n;
+  // up to 128 x 128 the matrix fits one workgroup's LDS: the same sweeps
+  // and stopping rule in two launches, without a host round trip per sweep
+  if (n <= kLdsEigMax && sym_eig_batched(st, n, 1, A, V0, w, V, work)) return;
   double *base = static_cast<double *>(work.ensure(sizeof(double) * (2 * nn + 4)));
   double *Vw = base;
   double *A2 = base + nn;
@@ -746,10 +830,6 @@ void sym_eig(hipStream_t st, int n, double *A, double *w, double *V, DevBuf &wor
     k_eye<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(n, Vw);
     check_launch("k_eye");
   }
-  // up to 128 x 128 the matrix fits one workgroup's LDS: the same sweeps
-  // and stopping rule in a single launch, without a host round trip per
-  // sweep
-  if (n <= kLdsEigMax && sym_eig_batched(st, n, 1, A, Vw, w, V)) return;
   const int m = n + (n & 1);
   const int npair = m / 2;
   const int tp = (npair + kJT - 1) / kJT;

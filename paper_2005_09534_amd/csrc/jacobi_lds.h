@@ -51,168 +51,230 @@ __device__ __forceinline__ void jacobi_rotation(const double *A, int n, int m, i
   jacobi_angle(A, n, rr_index(k, r, m), rr_index(m - 1 - k, r, m), p, q, c, s);
 }
 
-// Largest matrix that fits (12 KB of LDS besides it), and the largest whose eigenvectors fit beside it (149 KB of 160).
+// Largest matrix that fits (10 KB of LDS besides it).
 constexpr int kLdsEigMax = 128;
-constexpr int kLdsVecMax = 96;
 constexpr int kEigThreads = 1024;
-constexpr int kEigRed = kEigThreads;  // doubles of LDS for the reductions
+constexpr int kEigSweeps = 40;  // at most (about 8 are usual)
+constexpr int kEigRed = 2 * kLdsEigMax;  // doubles of LDS for sums and ranks
 
-// The rotations of a round: pair k's indices p, q as byte offsets in
-// a row (8 p, 8 q) and of rows, and (c, s).
+// A round's rotations (c, s), for pair k's indices in their order of
+// positions: s changes its sign with the order.
 struct JacobiRot {
-  int4 at[2][kLdsEigMax / 2];
   double2 cs[2][kLdsEigMax / 2];
 };
 __host__ __device__ constexpr int eig_even(int n) { return n + (n & 1); }
-// Doubles from one row of the LDS matrices to the next: odd, so that a column's
+// Doubles from one row of the LDS matrix to the next: odd, so that a column's
 // elements fall into different banks (n = 64: 0.9 ms with rows of 64 doubles).
 __host__ __device__ constexpr int eig_ld(int n) { return eig_even(n) + 1; }
 
-enum { kVecNone = 0, kVecLds = 1, kVecGlobal = 2 };
-
 // Sweeps over sA (LDS) until its off-diagonal Frobenius norm is 1e-14 of the
-// diagonal's or stops falling; rotations accumulate onto V.  sA is m x m (rows
-// eig_ld apart), m = n rounded up to even, its last row and column zero where n
-// is odd (the rotations of that index are the identity); V is n rows eig_ld
-// apart (kVecLds) or n in global memory (kVecGlobal); unused with kVecNone.
-// All threads.
+// diagonal's or stops falling; returns the number of rounds.  sA is m x m
+// (rows eig_ld apart), m = n <= NM rounded up to even, its last row and column
+// zero where n is odd (the rotations of that index are the identity).  All
+// threads.  Round i's rotations go to log[i m/2 .. (i + 1) m/2) as well (LOOK;
+// null: nowhere).
 //
-// A round is two phases: the first applies the round's rotations to A (the
-// blocks on and above the diagonal, each mirrored); in the second, the first
-// wave works out the next round's (a serial chain) while the other waves
-// apply this round's to V.  With V in global memory its loads go in one batch
-// a round.  One matrix from scratch, before and after (us): n = 33 309 and 190, n =
-// 64 1068 and 612, n = 96 2931 and 1602, n = 128 7090 and 6237 (LDS reads and
-// writes bound it: about 30 cycles for each wave of blocks and of V places).
-template <int VM>
-__device__ void jacobi_sweeps(int n, double *sA, double *V, double *red, JacobiRot &rot,
-                              int max_sweeps) {
+// A round is two phases.  LOOK, for one matrix alone on its CU, where latency
+// bounds it: all 2 x 2 blocks of A are read; then they are turned and written
+// back, each mirrored, while the first wave works out the next round's
+// rotations (a serial chain) from the entries that it has read and turned for
+// itself.  Without LOOK, which takes half the registers, so that two
+// workgroups share a CU and the LDS bounds them: all blocks of the upper
+// triangle are turned, then the first wave works out the next round's.  The
+// indices of a block go on by one a round in registers, so that its loads wait
+// for the barrier alone.  The entropies of L = 16 take 737 us without LOOK,
+// 804 mirrored too, 1093 with it, and took 1160 with the indices in LDS.
+template <int NM, bool LOOK>
+__device__ int jacobi_sweeps(int n, double *sA, double *red, JacobiRot &rot, int max_sweeps,
+                             double2 *log) {
   const int t = threadIdx.x;
   constexpr int nt = kEigThreads;
   const int m = eig_even(n), ld = eig_ld(n);
   const int npair = m / 2;
+  const int wrap = 8 * m;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   char *Ac = reinterpret_cast<char *>(sA);
-  auto el = [&](int byte) -> double & { return *reinterpret_cast<double *>(Ac + byte); };
-  // the 2 x 2 blocks (pair k1 rows, pair k2 >= k1 columns) of this thread, and
-  // its (row, pair) places of V
-  constexpr int kHalf = kLdsEigMax / 2;
-  constexpr int kA = (kHalf * (kHalf + 1) / 2 + nt - 1) / nt;         // 3
-  constexpr int kVmax = VM == kVecLds ? kLdsVecMax : kLdsEigMax;
-  constexpr int kV = (kVmax * (kVmax / 2) + nt - 64 - 1) / (nt - 64);  // 5 or 9
-  int ak[kA];  // k1 | k2 << 8
+  auto el = [&](int i, int j) -> double & {  // of indices times 8
+    return *reinterpret_cast<double *>(
+        Ac + (LOOK ? __mul24(i, ld) + j : __mul24(min(i, j), ld) + max(i, j)));
+  };
+  // the index (times 8) at a position in the next round: one further, position
+  // 0 stays at index 0
+  auto next = [&](int &x, bool moves) {
+    const int y = x + 8 == wrap ? 8 : x + 8;
+    x = moves ? y : x;
+  };
+  // waves 1 ..: the 2 x 2 blocks (pair k1 rows, pair k2 >= k1 columns) of this
+  // thread and the indices of their pairs' positions
+  constexpr int kHalf = NM / 2;
+  constexpr int kA = (kHalf * (kHalf + 1) / 2 + nt - 64 - 1) / (nt - 64);  // 1 or 3
+  int k1[kA], k2[kA], x1[kA], y1[kA], x2[kA], y2[kA];
 #pragma unroll
   for (int u = 0; u < kA; ++u) {
-    int idx = t + u * nt, k1 = 0;
-    ak[u] = -1;
-    if (idx < npair * (npair + 1) / 2) {
-      while (idx >= npair - k1) idx -= npair - k1++;  // row k1 holds k2 = k1 .. npair - 1
-      ak[u] = k1 | ((k1 + idx) << 8);
+    int idx = t - 64 + u * (nt - 64), k = 0;
+    k1[u] = -1;
+    k2[u] = x1[u] = y1[u] = x2[u] = y2[u] = 0;
+    if (t >= 64 && idx < npair * (npair + 1) / 2) {
+      while (idx >= npair - k) idx -= npair - k++;  // row k holds k2 = k .. npair - 1
+      k1[u] = k;
+      k2[u] = k + idx;
+      x1[u] = 8 * k;
+      y1[u] = 8 * (m - 1 - k);
+      x2[u] = 8 * (k + idx);
+      y2[u] = 8 * (m - 1 - k - idx);
     }
   }
-  int vk[kV];  // row's first element | k << 16
-#pragma unroll
-  for (int u = 0; u < kV; ++u) {
-    const int idx = t - 64 + u * (nt - 64);
-    vk[u] = (VM != kVecNone && t >= 64 && idx < n * npair)
-                ? ((idx / npair) * (VM == kVecLds ? ld : n) | ((idx % npair) << 16))
-                : -1;
+  // wave 0: pair t of the next round is the index at its position k + 1 of now
+  // (position 0 stays) with the one at m - k (position m - 1 takes position
+  // 1's): the first (0) or second (1) of pairs jt and jb of now
+  int jt = t + 1, jb = t - 1, st = 0, sb = 1;
+  if (t == 0) {
+    jt = 0;
+    jb = npair > 1 ? 1 : 0;
+    sb = npair > 1 ? 0 : 1;
+  } else if (t == npair - 1) {
+    jt = t;
+    st = 1;
   }
-  // this thread's pair: positions t and m - 1 - t, their indices of round 0
-  // (x, y; one further each round, position 0 stays at index 0)
-  auto rotate = [&](int x, int y, int b) {
-    if (t >= npair) return;
-    const int p = x < y ? x : y, q = x < y ? y : x;
-    const double apq = sA[p * ld + q];
+  const bool looks = t < npair;
+  if (!looks) jt = jb = 0;
+  int tt = 8 * jt, tb = 8 * (m - 1 - jt), bt = 8 * jb, bb = 8 * (m - 1 - jb);
+  int xr = 8 * t, yr = 8 * (m - 1 - t);  // pair t of now
+  auto angle = [&](int b) {
+    const double apq = el(xr, yr);
     double c = 1.0, s = 0.0;
-    if (apq != 0.0) jacobi_cs(apq, sA[q * ld + q] - sA[p * ld + p], c, s);
-    rot.at[b][t] = make_int4(8 * p, 8 * q, 8 * p * ld, 8 * q * ld);
+    if (apq != 0.0) jacobi_cs(apq, el(yr, yr) - el(xr, xr), c, s);
     rot.cs[b][t] = make_double2(c, s);
   };
+  if (looks) angle(0);
+  // one block: its entries, and these turned and written back
+  auto load = [&](int u, double (&a)[4]) {
+    a[0] = el(x1[u], x2[u]);
+    a[1] = el(x1[u], y2[u]);
+    a[2] = el(y1[u], x2[u]);
+    a[3] = el(y1[u], y2[u]);
+  };
+  auto turn = [&](int u, int b, const double (&a)[4]) {
+    const double2 r1 = rot.cs[b][k1[u]], r2 = rot.cs[b][k2[u]];
+    const double b00 = r1.x * a[0] - r1.y * a[2], b01 = r1.x * a[1] - r1.y * a[3];
+    const double b10 = r1.y * a[0] + r1.x * a[2], b11 = r1.y * a[1] + r1.x * a[3];
+    const double d00 = b00 * r2.x - b01 * r2.y, d01 = b00 * r2.y + b01 * r2.x;
+    const double d10 = b10 * r2.x - b11 * r2.y, d11 = b10 * r2.y + b11 * r2.x;
+    el(x1[u], x2[u]) = d00;
+    el(x1[u], y2[u]) = d01;
+    if (LOOK || k1[u] != k2[u]) el(y1[u], x2[u]) = d10;
+    el(y1[u], y2[u]) = d11;
+    if (LOOK && k1[u] != k2[u]) {
+      el(x2[u], x1[u]) = d00;
+      el(y2[u], x1[u]) = d01;
+      el(x2[u], y1[u]) = d10;
+      el(y2[u], y1[u]) = d11;
+    }
+    next(x1[u], k1[u] > 0);
+    next(x2[u], k2[u] > 0);
+    next(y1[u], true);
+    next(y2[u], true);
+  };
+  __syncthreads();
   double prev = -1.0;
-  int b = 0;
+  int b = 0, rounds = 0;
   for (int sweep = 0; sweep < max_sweeps && n > 1; ++sweep) {
-    int x = rr_index(t, 0, m), y = rr_index(m - 1 - t, 0, m);
-    rotate(x, y, b);
-    __syncthreads();
     for (int r = 0; r < m - 1; ++r) {
       // A <- J^T A J: the blocks are disjoint, each read and written by one
       // thread
+      if constexpr (!LOOK) {
 #pragma unroll
-      for (int u = 0; u < kA; ++u) {
-        if (ak[u] < 0) continue;
-        const int k1 = ak[u] & 255, k2 = ak[u] >> 8;
-        const int4 e1 = rot.at[b][k1], e2 = rot.at[b][k2];
-        const double2 r1 = rot.cs[b][k1], r2 = rot.cs[b][k2];
-        const double a00 = el(e1.z + e2.x), a01 = el(e1.z + e2.y);
-        const double a10 = el(e1.w + e2.x), a11 = el(e1.w + e2.y);
-        const double b00 = r1.x * a00 - r1.y * a10, b01 = r1.x * a01 - r1.y * a11;
-        const double b10 = r1.y * a00 + r1.x * a10, b11 = r1.y * a01 + r1.x * a11;
-        const double d00 = b00 * r2.x - b01 * r2.y, d01 = b00 * r2.y + b01 * r2.x;
-        const double d10 = b10 * r2.x - b11 * r2.y, d11 = b10 * r2.y + b11 * r2.x;
-        el(e1.z + e2.x) = d00;
-        el(e1.z + e2.y) = d01;
-        el(e1.w + e2.x) = d10;
-        el(e1.w + e2.y) = d11;
-        if (k1 != k2) {
-          el(e2.z + e1.x) = d00;
-          el(e2.w + e1.x) = d01;
-          el(e2.z + e1.y) = d10;
-          el(e2.w + e1.y) = d11;
+        for (int u = 0; u < kA; ++u) {
+          if (k1[u] < 0) continue;
+          double a[4];
+          load(u, a);
+          turn(u, b, a);
         }
+        __syncthreads();
+        next(xr, t > 0);
+        next(yr, true);
+        if (looks) angle(b ^ 1);
+      } else if (wave == 0) {
+        double p00 = 0, p01 = 0, p11 = 0, q00 = 0, q01 = 0, q11 = 0;
+        double z00 = 0, z01 = 0, z10 = 0, z11 = 0;
+        double2 r1 = make_double2(1.0, 0.0), r2 = r1;
+        if (looks) {
+          r1 = rot.cs[b][jt];
+          r2 = rot.cs[b][jb];
+          p00 = el(tt, tt);
+          p01 = el(tt, tb);
+          p11 = el(tb, tb);
+          q00 = el(bt, bt);
+          q01 = el(bt, bb);
+          q11 = el(bb, bb);
+          z00 = el(tt, bt);
+          z01 = el(tt, bb);
+          z10 = el(tb, bt);
+          z11 = el(tb, bb);
+        }
+        __syncthreads();
+        if (looks) {
+          // the pair's first index turns into c first - s second, its second
+          // into s first + c second
+          const double f0 = st ? r1.y : r1.x, f1 = st ? r1.x : -r1.y;
+          const double g0 = sb ? r2.y : r2.x, g1 = sb ? r2.x : -r2.y;
+          const double axx = f0 * (f0 * p00 + f1 * p01) + f1 * (f0 * p01 + f1 * p11);
+          const double ayy = g0 * (g0 * q00 + g1 * q01) + g1 * (g0 * q01 + g1 * q11);
+          const double axy = f0 * (g0 * z00 + g1 * z01) + f1 * (g0 * z10 + g1 * z11);
+          double c = 1.0, s = 0.0;
+          if (axy != 0.0) jacobi_cs(axy, ayy - axx, c, s);
+          rot.cs[b ^ 1][t] = make_double2(c, s);
+          next(tt, jt > 0);
+          next(bt, jb > 0);
+          next(tb, true);
+          next(bb, true);
+        }
+      } else {
+        double a[kA][4];
+#pragma unroll
+        for (int u = 0; u < kA; ++u)
+          if (k1[u] >= 0) load(u, a[u]);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kA; ++u)
+          if (k1[u] >= 0) turn(u, b, a[u]);
+        if (log != nullptr && wave == nt / 64 - 1 && (t & 63) < npair)
+          log[(size_t)rounds * npair + (t & 63)] = rot.cs[b][t & 63];
       }
-      __syncthreads();
-      if (t > 0 && ++x == m) x = 1;
-      if (++y == m) y = 1;
-      if (r + 1 < m - 1) rotate(x, y, b ^ 1);
-      if (VM != kVecNone && t >= 64) {  // V <- V J (columns p, q of every row)
-        double vp[kV], vq[kV];
-#pragma unroll
-        for (int u = 0; u < kV; ++u) {
-          if (vk[u] < 0) continue;
-          const int4 e = rot.at[b][vk[u] >> 16];
-          if (VM == kVecGlobal && e.y == 8 * n) continue;
-          const char *v = reinterpret_cast<const char *>(V + (vk[u] & 0xffff));
-          vp[u] = *reinterpret_cast<const double *>(v + e.x);
-          vq[u] = *reinterpret_cast<const double *>(v + e.y);
-        }
-#pragma unroll
-        for (int u = 0; u < kV; ++u) {
-          if (vk[u] < 0) continue;
-          const int4 e = rot.at[b][vk[u] >> 16];
-          if (VM == kVecGlobal && e.y == 8 * n) continue;
-          const double2 cs = rot.cs[b][vk[u] >> 16];
-          char *v = reinterpret_cast<char *>(V + (vk[u] & 0xffff));
-          *reinterpret_cast<double *>(v + e.x) = cs.x * vp[u] - cs.y * vq[u];
-          *reinterpret_cast<double *>(v + e.y) = cs.y * vp[u] + cs.x * vq[u];
-        }
-      }
+      ++rounds;
       __syncthreads();
       b ^= 1;
     }
     // off-diagonal and diagonal sums of squares
     double off = 0.0, dg = 0.0;
-    for (int e = t; e < m * m; e += nt) {
-      const double v = sA[(e / m) * ld + e % m];
-      if (e / m == e % m) dg += v * v; else off += v * v;
-    }
-    auto total = [&](double x) {
-      red[t] = x;
-      __syncthreads();
-      for (int h = nt / 2; h > 0; h >>= 1) {
-        if (t < h) red[t] += red[t + h];
-        __syncthreads();
+    for (int i = wave; i < m; i += nt / 64)
+      for (int j = t & 63; j < m; j += 64) {
+        const double x = sA[i * ld + j];
+        if (i == j) dg += x * x; else if (i < j) off += 2.0 * (x * x);
       }
-      const double r = red[0];
-      __syncthreads();
-      return r;
-    };
-    const double o = total(off), d = total(dg);
+#pragma unroll
+    for (int h = 32; h >= 1; h >>= 1) {
+      off += __shfl_xor(off, h);
+      dg += __shfl_xor(dg, h);
+    }
+    if ((t & 63) == 0) {
+      red[t >> 6] = off;
+      red[nt / 64 + (t >> 6)] = dg;
+    }
+    __syncthreads();
+    double o = 0.0, d = 0.0;
+    for (int i = 0; i < nt / 64; ++i) {
+      o += red[i];
+      d += red[nt / 64 + i];
+    }
+    __syncthreads();
     // stop at a relative off-diagonal norm of 1e-14, or when the rounding
     // floor is reached (no further decrease)
     if (!(o > 1e-28 * d) || o == 0.0) break;
     if (prev >= 0.0 && sweep >= 3 && o > 0.5 * prev) break;
     prev = o;
   }
+  return rounds;
 }
 
 }  // namespace polfed

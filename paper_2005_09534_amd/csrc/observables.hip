@@ -67,7 +67,7 @@ struct EntBlocks {
 // that matrix's eigenvalues lambda, all in LDS, then part = -sum lambda ln
 // lambda (ascending).  Blocks of every size in one launch, the largest first:
 // one launch a size left most of the chip idle (L = 16, 20 vectors, 8 cuts:
-// 160 workgroups of each of 9 sizes, 4.7 ms in all; 1.15 ms so), with the
+// 160 workgroups of each of 9 sizes, 4.7 ms in all; 0.74 ms so), with the
 // eigenvectors, which nothing needs, half of each.
 __global__ __launch_bounds__(kEigThreads) void k_ent_blocks(long long n, int pairs, EntBlocks eb,
                                                             const double *M, double *part) {
@@ -88,7 +88,10 @@ __global__ __launch_bounds__(kEigThreads) void k_ent_blocks(long long n, int pai
     sA[k * ld + i] = acc;
   }
   __syncthreads();
-  jacobi_sweeps<kVecNone>(d, sA, nullptr, red, rot, 40);
+  if (d <= 64)
+    jacobi_sweeps<64, false>(d, sA, red, rot, kEigSweeps, nullptr);
+  else
+    jacobi_sweeps<128, false>(d, sA, red, rot, kEigSweeps, nullptr);
   __syncthreads();
   double *lam = red;
   for (int i = threadIdx.x; i < d; i += kEigThreads) {

@@ -2050,7 +2050,8 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
                 sizeof(double) * (3 * mm + msz) * nd));
             double *V0all = Aall + mm * nd, *Vall = V0all + mm * nd, *wall = Vall + mm * nd;
             for (size_t k = 0; k < nd; ++k) rs[dz[k]]->check_prepare(Aall + k * mm, V0all + k * mm);
-            batched = sym_eig_batched(st, msz, (int)nd, Aall, V0all, wall, Vall);
+            batched = sym_eig_batched(st, msz, (int)nd, Aall, V0all, wall, Vall,
+                                      ctx->buf("eig_log"));
             if (batched) {
               PF_HIP(hipStreamSynchronize(st));
               const double share = (now_s() - te0) / nd;

@@ -36,6 +36,30 @@ def test_lds_jacobi_edges(ctx, n, scale):
     assert np.abs(V.T @ V - np.eye(n)).max() <= 1e-12
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 64, 65, 66, 128])
+@pytest.mark.parametrize("kind", ["full", "diagonal", "rank one", "pairs"])
+def test_lds_jacobi_log(ctx, n, kind):
+    """Both sizes of the rotation log at their edges, rounds of identities, and
+    equal eigenvalues."""
+    import torch
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n))
+    A = A + A.T
+    if kind == "diagonal":
+        A = np.diag(np.diag(A))
+    elif kind == "rank one":
+        A = np.ones((n, n))
+    elif kind == "pairs":
+        A = np.kron(np.eye((n + 1) // 2), np.array([[1.0, 2.0], [2.0, 1.0]]))[:n, :n]
+    w, V = (x.cpu().numpy() for x in ctx.sym_eig(torch.from_numpy(A.copy()).cuda()))
+    norm = max(np.abs(A).sum(axis=1).max(), 1e-300)
+    # as above
+    assert np.all(np.diff(w) >= 0)
+    assert np.abs(w - np.linalg.eigvalsh(A)).max() <= 1e-12 * norm
+    assert np.abs(A @ V - V * w).max() <= 1e-12 * norm
+    assert np.abs(V.T @ V - np.eye(n)).max() <= 1e-12
+
+
 @pytest.mark.parametrize("L,nvec,cuts", [(2, 1, [0, 1]), (4, 3, [0, 3]), (6, 2, [5]),
                                          (10, 130, [0, 1, 2, 3, 4]), (18, 2, [0, 8])])
 def test_entropies_of_random_vectors(ctx, pf, L, nvec, cuts):
