@@ -412,24 +412,39 @@ void launch_update(hipStream_t st, long long n, int p, int q, double alpha, cons
 
 // --------------------------------------------------------- small gemm --
 
-__global__ void k_small_gemm(int m, int l, int k, const double *A, int lda, const double *B,
-                             int ldb, double *C, int ldc, int transA) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
+// The products are small and each entry is one chain of l sums, so latency
+// bounds it: eight terms' loads at once, and a wave a workgroup, so that they
+// spread over the chip (the products of a solve with bases of up to 90
+// columns: 9.0 us each one by one, 3.9 so).
+__global__ __launch_bounds__(64) void k_small_gemm(int m, int l, int k, const double *A, int lda,
+                                                   const double *B, int ldb, double *C, int ldc,
+                                                   int transA) {
+  const int e = blockIdx.x * 64 + threadIdx.x;
   if (e >= m * k) return;
-  int i = e / k, j = e % k;
+  const int i = e / k, j = e % k;
+  const double *a = A + (transA ? (size_t)i : (size_t)i * lda), *b = B + j;
+  const size_t step = transA ? lda : 1;
   double s = 0.0;
-  for (int t = 0; t < l; ++t) {
-    double a = transA ? A[(size_t)t * lda + i] : A[(size_t)i * lda + t];
-    s += a * B[(size_t)t * ldb + j];
+  int t = 0;
+  for (; t + 8 <= l; t += 8) {
+    double x[8], y[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x[u] = a[(t + u) * step];
+      y[u] = b[(size_t)(t + u) * ldb];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += x[u] * y[u];
   }
+  for (; t < l; ++t) s += a[t * step] * b[(size_t)t * ldb];
   C[(size_t)i * ldc + j] = s;
 }
 
 void launch_small_gemm(hipStream_t st, int m, int l, int k, const double *A, int lda,
                        const double *B, int ldb, double *C, int ldc, int transA) {
   if (m <= 0 || k <= 0) return;
-  int tot = m * k;
-  k_small_gemm<<<(tot + 255) / 256, 256, 0, st>>>(m, l, k, A, lda, B, ldb, C, ldc, transA);
+  const int tot = m * k;
+  k_small_gemm<<<(tot + 63) / 64, 64, 0, st>>>(m, l, k, A, lda, B, ldb, C, ldc, transA);
   check_launch("k_small_gemm");
 }
 
@@ -936,12 +951,16 @@ __global__ __launch_bounds__(256) void k_colsq(long long n, int q, const double 
     part[(size_t)blockIdx.x * q + col] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
-__global__ void k_colsum_final(int q, int nblk, const double *part, double *out, int do_sqrt) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= q) return;
+// One wave a column: a single thread's chain of loads took 17 us over 512
+// blocks; so under 8.
+__global__ __launch_bounds__(64) void k_colsum_final(int q, int nblk, const double *part,
+                                                     double *out, int do_sqrt) {
+  const int j = blockIdx.x, lane = threadIdx.x;
   double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += part[(size_t)b * q + j];
-  out[j] = do_sqrt ? sqrt(s) : s;
+  for (int b = lane; b < nblk; b += 64) s += part[(size_t)b * q + j];
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  if (lane == 0) out[j] = do_sqrt ? sqrt(s) : s;
 }
 
 static void colsq(hipStream_t st, int mode, long long n, int q, const double *X, long long ldx,
@@ -958,7 +977,7 @@ static void colsq(hipStream_t st, int mode, long long n, int q, const double *X,
   else
     k_colsq<1><<<grid, 256, 0, st>>>(n, q, X, ldx, V, ldv, E, part, rows);
   check_launch("k_colsq");
-  k_colsum_final<<<(q + 255) / 256, 256, 0, st>>>(q, (int)nblk, part, out, 1);
+  k_colsum_final<<<q, 64, 0, st>>>(q, (int)nblk, part, out, 1);
   check_launch("k_colsum_final");
 }
 
@@ -1006,18 +1025,27 @@ __global__ __launch_bounds__(256) void k_colargmax(long long n, int q, const dou
   }
 }
 
-__global__ void k_sign_final(int q, int nblk, const double *pv, const long long *pi,
-                             const double *X, long long ldx, double *f) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= q) return;
+// One wave a column (a single thread took 73 us over 512 blocks).
+__global__ __launch_bounds__(64) void k_sign_final(int q, int nblk, const double *pv,
+                                                   const long long *pi, const double *X,
+                                                   long long ldx, double *f) {
+  const int j = blockIdx.x, lane = threadIdx.x;
   double best = -1.0;
   long long bidx = -1;
-  for (int b = 0; b < nblk; ++b) {
-    const double v = pv[(size_t)b * q + j];
-    const long long i = pi[(size_t)b * q + j];
-    if (v > best || (v == best && i >= 0 && (bidx < 0 || i < bidx))) { best = v; bidx = i; }
+  auto take = [&](double v, long long i) {
+    if (v > best || (v == best && i >= 0 && (bidx < 0 || i < bidx))) {
+      best = v;
+      bidx = i;
+    }
+  };
+  for (int b = lane; b < nblk; b += 64) take(pv[(size_t)b * q + j], pi[(size_t)b * q + j]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double v = __shfl_xor(best, o);
+    const long long i = __shfl_xor(bidx, o);
+    take(v, i);
   }
-  f[j] = (bidx >= 0 && X[bidx * ldx + j] < 0.0) ? -1.0 : 1.0;
+  if (lane == 0) f[j] = (bidx >= 0 && X[bidx * ldx + j] < 0.0) ? -1.0 : 1.0;
 }
 
 void launch_sign_factors(hipStream_t st, long long n, int q, const double *X, long long ldx,
@@ -1032,7 +1060,7 @@ void launch_sign_factors(hipStream_t st, long long n, int q, const double *X, lo
   dim3 grid((unsigned)nblk, (unsigned)((q + 63) / 64));
   k_colargmax<<<grid, 256, 0, st>>>(n, q, X, ldx, pv, pi, rows);
   check_launch("k_colargmax");
-  k_sign_final<<<(q + 255) / 256, 256, 0, st>>>(q, (int)nblk, pv, pi, X, ldx, f);
+  k_sign_final<<<q, 64, 0, st>>>(q, (int)nblk, pv, pi, X, ldx, f);
   check_launch("k_sign_final");
 }
 
@@ -1118,14 +1146,12 @@ void launch_fill(hipStream_t st, double *x, long long count, double v) {
 constexpr int kRedThreads = 256;
 
 __device__ double block_sum(double v, double *sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if (t < w) sh[t] += sh[t + w];
-    __syncthreads();
-  }
-  double r = sh[0];
+  double r = 0.0;
+  for (int w = 0; w < (int)blockDim.x / 64; ++w) r += sh[w];
   __syncthreads();
   return r;
 }
@@ -1138,7 +1164,7 @@ __device__ double sum_partials(const double *part, int nblk, double *sh, int str
 
 __global__ __launch_bounds__(kRedThreads) void k_dot_partials(long long n, const double *x,
                                                               const double *y, double *part) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[kRedThreads / 64];
   double s = 0.0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -1154,7 +1180,7 @@ __global__ __launch_bounds__(kRedThreads) void k_lanczos_update(long long n, dou
                                                                 double *alpha,
                                                                 const double *beta_prev,
                                                                 double *part2) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[kRedThreads / 64];
   const double a = sum_partials(part, npart, sh, stride);
   const double b = (vprev != nullptr) ? beta_prev[0] : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) alpha[0] = a;
@@ -1174,7 +1200,7 @@ __global__ __launch_bounds__(kRedThreads) void k_lanczos_normalize(long long n, 
                                                                    double *vnext,
                                                                    const double *part2, int nblk,
                                                                    double *beta) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[kRedThreads / 64];
   const double b = sqrt(sum_partials(part2, nblk, sh));
   if (blockIdx.x == 0 && threadIdx.x == 0) beta[0] = b;
   const double inv = (b > 1e-300) ? 1.0 / b : 0.0;
