@@ -43,7 +43,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 FP64_MFMA_PEAK_TFLOPS = 78.6   # MI355X dense FP64 matrix
 METRIC = "H·V applications/s (achieved HBM GB/s) + time to N_ev eigenpairs, FP32 vs FP64"
-STEP_SOURCES = ("hv_kernels.h", "hv.hip", "hv_f32.hip")
+STEP_SOURCES = ("segment.hip",)
 
 
 def _kernel_hash():
@@ -354,7 +354,8 @@ def main():
                                        "t_refine", "t_total", "max_resid", "normH", "n_conv",
                                        "refine_passes")},
         "roofline": {
-            "kernel": "k_step (fused Chebyshev step: matrix-free H~ gather + 3-term update)",
+            "kernel": "k_segment (fused Chebyshev step: matrix-free H~ gather + 3-term update; "
+                      "chains of up to 4096 states: the whole filter, k_resident_*)",
             "bound": "hbm",
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,

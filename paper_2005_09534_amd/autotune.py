@@ -198,11 +198,10 @@ def tune_block(ctx, chains, nev, precision, widths=(4, 8, 16, 32), cache=None, s
         run()  # warm (graph capture, buffers)
         st, t = timed()
         if len(models) > 1:
-            # the batched kernel has shapes of its own (a launch walks many
-            # realisations; a single chain's tuned shape, chosen where a
-            # launch is short, can be far off there): re-time the
-            # groups-per-CU choice of the batch shape on the sample batch,
-            # keep a change only when it gains more than 3%
+            # batches have shapes of their own, kept and reported (the batched
+            # kernels choose their launches by size alone): re-time the
+            # groups-per-CU entry on the sample batch, keep a change only when
+            # it gains more than 3%
             base = tuple(ctx.get_batch_shape(L, s, precision))
             best_sh, best_st, best_t = base, st, t
             for wpc in (2, 4, 8, 16):

@@ -1209,6 +1209,23 @@ __global__ __launch_bounds__(kRedThreads) void k_lanczos_normalize(long long n, 
     vnext[i] = w[i] * inv;
 }
 
+// part[b] = sum of the b-th of gridDim.x parts of x[0], x[2], ..., x[2 count - 2].
+__global__ __launch_bounds__(kRedThreads) void k_sum_chunks(int count, const double *x,
+                                                            double *part) {
+  __shared__ double sh[kRedThreads / 64];
+  const int per = (count + gridDim.x - 1) / gridDim.x;
+  const int i0 = blockIdx.x * per, i1 = min(count, i0 + per);
+  double s = 0.0;
+  for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) s += x[(size_t)2 * i];
+  s = block_sum(s, sh);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
+void launch_sum_chunks(hipStream_t st, int count, const double *x, double *part, int nblk) {
+  k_sum_chunks<<<nblk, kRedThreads, 0, st>>>(count, x, part);
+  check_launch("k_sum_chunks");
+}
+
 void launch_dot_partials(hipStream_t st, long long n, const double *x, const double *y,
                          double *part, int nblk) {
   k_dot_partials<<<nblk, kRedThreads, 0, st>>>(n, x, y, part);

@@ -291,7 +291,7 @@ template <class T>
 void launch_from_slices(hipStream_t st, long long n, int S, const T *packed, T *Y, long long ldy);
 
 // Built-in default shapes (used when the context holds no tuned entry) of
-// the single-chain and the batched step kernel.
+// the step kernel, single-chain and (reported only) batched.
 StepShape default_shape(int L, int S, bool fp32);
 StepShape default_batch_shape(int L, int S, bool fp32);
 
@@ -385,6 +385,7 @@ void launch_symmetrize(hipStream_t st, int s, double *A, int lda);
 // Bounds Lanczos helpers (single vector, FP64, scalars on device).
 void launch_dot_partials(hipStream_t st, long long n, const double *x, const double *y,
                          double *part, int nblk);
+void launch_sum_chunks(hipStream_t st, int count, const double *x, double *part, int nblk);
 void launch_lanczos_update(hipStream_t st, long long n, double *w, const double *v,
                            const double *vprev, const double *part, int npart, int stride,
                            int nblk, double *alpha, const double *beta_prev, double *part2);
@@ -464,12 +465,12 @@ struct polfed_ctx {
   // launch shapes of the step kernel chosen by the autotuner, keyed by
   // (L, block width, precision bytes)
   std::map<std::tuple<int, int, int>, polfed::StepShape> shapes;
-  // launch shapes of the batched step kernel (same key); its rank mode is
-  // always the tables and its column slices 1
+  // launch shapes set for batched launches (same key): kept and reported, the
+  // batched kernels take none
   std::map<std::tuple<int, int, int>, polfed::StepShape> batch_shapes;
   // block sizes chosen by the autotuner, keyed by (L, precision, nev)
   std::map<std::tuple<int, int, int>, int> blocks;
-  // cached HIP graph of one whole filter application (K+1 step launches),
+  // cached HIP graph of one whole filter application by k_step launches,
   // replayed for every Lanczos block; keyed by everything baked into it
   hipGraphExec_t filter_graph = nullptr;
   std::vector<unsigned long long> filter_graph_key;

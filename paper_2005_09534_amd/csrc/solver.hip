@@ -491,6 +491,21 @@ static void run_resident_batch(polfed_ctx *ctx, std::vector<std::pair<int, ResIt
   }
 }
 
+// Algorithmic bytes of a Clenshaw filter that the step kernel does not run
+// (its byte model: each streamed block once per step, the state word and
+// diagonal of every row where H~ is applied).
+template <class T>
+static double clenshaw_bytes(long long n, int S, long long K, const std::vector<double> &coef) {
+  double mv = 0.0;
+  for (long long jj = 0; jj < K; ++jj) {
+    const int streams = 1 + (jj >= 1) + (jj >= 2) + (coef[K - jj] != 0.0);
+    mv += (double)n * (S * (double)sizeof(T) * streams + (jj >= 1 ? 4.0 + sizeof(T) : 0.0));
+  }
+  mv += (double)n * (S * (double)sizeof(T) * (2 + (K >= 1) + (K >= 2)) +
+                     (K >= 1 ? 4.0 + sizeof(T) : 0.0));
+  return mv;
+}
+
 template <class T>
 static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, int S,
                        const T *X, long long ldx, T *Y, long long ldy, long long K,
@@ -507,18 +522,14 @@ static void run_filter(polfed_ctx *ctx, const Chain &c, const T *dt, double a, i
   const int form = ctx->filter_form;
   if (use_resident<T>(shape, form, n, S)) {
     run_resident<T>(ctx, c, dt, a, S, X, ldx, Y, ldy, K, coef, D);
-    moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
-                            D, buf3, form, nullptr, false);
-    finish_filter_stats(ctx, moved, (double)(K + 1), bytes);
+    finish_filter_stats(ctx, clenshaw_bytes<T>(n, S, K, coef), (double)(K + 1), bytes);
     return;
   }
   if (K >= 1 && form == POLFED_FORM_CLENSHAW && use_segments(shape, c.L)) {
     ctx->seg_table(c.L);
     PF_HIP(hipEventRecord(ctx->ev_start, ctx->stream));
     queue_filter_segments<T>(ctx, c, dt, a, S, X, ldx, Y, ldy, K, coef, D, buf3);
-    moved = queue_filter<T>(ctx->stream, ctx->num_cu, shape, c, dt, a, S, X, ldx, Y, ldy, K, coef,
-                            D, buf3, form, nullptr, false);
-    finish_filter_stats(ctx, moved, (double)(K + 1), bytes);
+    finish_filter_stats(ctx, clenshaw_bytes<T>(n, S, K, coef), (double)(K + 1), bytes);
     return;
   }
   // the slice-major copy of X (allocated before any capture)
@@ -682,6 +693,7 @@ void run_bounds(polfed_ctx *ctx, const Chain &c, int steps, unsigned long long s
   double *sums = seg ? static_cast<double *>(ctx->buf("bnd_sums").ensure(
                            sizeof(double) * 2 * (size_t)table->nseg))
                      : nullptr;
+  const int nsum = std::min(nblk, 256);
   if (!seg) attach_pattern(ctx, c, shape);
   for (int k = 0; k < steps; ++k) {
     double *vk = v[k % 3];
@@ -699,8 +711,18 @@ void run_bounds(polfed_ctx *ctx, const Chain &c, int steps, unsigned long long s
       a.w2 = 0.5 * c.J2;
       a.dots = sums;
       launch_segment<double>(st, c.L, c.J2 != 0.0, 1, *table, a);
-      launch_lanczos_update(st, n, w, vk, vprev, sums + 1, table->nseg, 2, nblk, alpha + k,
-                            beta + k, part2);
+      // every workgroup of the update adds the sums up: many go through one
+      // launch more (L = 26, 65 thousand: 301 us a step without it, 241 so)
+      const double *dots = sums + 1;
+      int ndots = table->nseg, stride = 2;
+      if (ndots > 4096) {
+        launch_sum_chunks(st, ndots, dots, part, nsum);
+        dots = part;
+        ndots = nsum;
+        stride = 1;
+      }
+      launch_lanczos_update(st, n, w, vk, vprev, dots, ndots, stride, nblk, alpha + k, beta + k,
+                            part2);
     } else {
       StepArgs<double> a = base_args<double>(c, c.diag.as<double>());
       a.V = vk;
@@ -1667,21 +1689,6 @@ int solve_one(polfed_ctx *ctx, const polfed_model *model, const polfed_opts *opt
 // time, with the filters of its active members in shared launches
 // (run_filter_batch): one for all steps of the short chains, one a step for
 // the others.
-// Algorithmic bytes of one realisation's batched Clenshaw filter (the byte
-// model of the single-chain filter: each streamed block once per step, the
-// state word and diagonal of every row where H~ is applied).
-template <class T>
-static double batched_filter_bytes(long long n, int S, long long K, const std::vector<double> &coef) {
-  double mv = 0.0;
-  for (long long jj = 0; jj < K; ++jj) {
-    const int streams = 1 + (jj >= 1) + (jj >= 2) + (coef[K - jj] != 0.0);
-    mv += (double)n * (S * (double)sizeof(T) * streams + (jj >= 1 ? 4.0 + sizeof(T) : 0.0));
-  }
-  mv += (double)n * (S * (double)sizeof(T) * (2 + (K >= 1) + (K >= 2)) +
-                     (K >= 1 ? 4.0 + sizeof(T) : 0.0));
-  return mv;
-}
-
 // One member of a batched filter: its chain, blocks (buf: 3 n S values for the
 // recurrence) and filter.
 template <class T>
@@ -1882,7 +1889,7 @@ static void refine_batched(polfed_ctx *ctx, std::vector<std::unique_ptr<Realizat
           const double f = (double)r.n * (r.K_r + 1) / wsum;
           r.filter_gpu_s += 1e-3 * ms * f;
           r.filter_launches += (double)(Kmax + 1) * f;
-          r.refine_bytes += batched_filter_bytes<double>(r.n, w, r.K_r, r.coef_r);
+          r.refine_bytes += clenshaw_bytes<double>(r.n, w, r.K_r, r.coef_r);
         }
         k0 = k1;
       }
@@ -2019,7 +2026,7 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
         glaunch += (double)(steps + 1);
         // algorithmic bytes of the active members (same model as one filter)
         for (int i = 0; i < B; ++i)
-          if (act[i]) rs[i]->bytes += batched_filter_bytes<T>(rs[i]->n, S, rs[i]->K, rs[i]->coef);
+          if (act[i]) rs[i]->bytes += clenshaw_bytes<T>(rs[i]->n, S, rs[i]->K, rs[i]->coef);
         const double tf = now_s() - tf0;
         for (int i = 0; i < B; ++i)
           if (act[i]) rs[i]->t_filter += tf / nact;

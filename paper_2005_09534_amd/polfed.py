@@ -404,8 +404,8 @@ class Context:
                     "set_batch_shape")
 
     def get_batch_shape(self, L, nvec, precision):
-        """(threads, lpl, wg_per_cu, lds_tables, early_loads, xcd_slices) of the
-        batched kernel."""
+        """(threads, lpl, wg_per_cu, lds_tables, early_loads, xcd_slices) kept
+        for batched launches."""
         out = [c_int() for _ in range(6)]
         self._check(LIB.polfed_get_batch_shape(self.h, L, nvec, precision,
                                                *[ctypes.byref(o) for o in out]), "get_batch_shape")

@@ -31,7 +31,7 @@ COPY_BYTES = 1 << 30
 WARMUP_K = 2
 
 
-STEP_SOURCES = ("hv_kernels.h", "hv.hip", "hv_f32.hip")
+STEP_SOURCES = ("segment.hip",)
 
 
 def kernel_source_hash():
@@ -98,7 +98,7 @@ def run(args):
 def _read(path, counter, step_name):
     """(per-dispatch values of `counter` for the step kernel instantiation
     `step_name` in the timed filter, largest value for the library's copy
-    kernel) from a rocprofv3 counter_collection CSV.  The WARMUP_K + 1
+    kernel) from a rocprofv3 counter_collection CSV.  The WARMUP_K
     dispatches of the warm-up filter come first and are left out."""
     step, copy = [], []
     with open(path) as f:
@@ -111,7 +111,7 @@ def _read(path, counter, step_name):
                 step.append((int(row.get("Dispatch_Id") or len(step)), v))
             elif "k_stream_copy" in name:
                 copy.append(v)
-    step = [v for _, v in sorted(step)[WARMUP_K + 1:]]
+    step = [v for _, v in sorted(step)[WARMUP_K:]]
     return step, (max(copy) if copy else 0.0)
 
 
@@ -119,9 +119,8 @@ def summarize(args):
     wl, precision = _workload(args.workload)
     T = "float" if precision == "fp32" else "double"
     s = wl.block if wl.block > 0 else 16
-    shape = [int(v) for v in args.shape.split(",")]
-    slices = shape[6] if len(shape) > 6 and s % shape[6] == 0 else 1
-    step_name = f"k_step<{T}, {s // slices},"  # the kernel's width is one slice
+    # one slice's width (the bounds run takes width 1)
+    step_name = f"k_segment<{T}, {min(s, 4 if precision == 'fp32' else 2)},"
     fs, fc = _read(args.fetch, "FETCH_SIZE", step_name)
     ws, wc = _read(args.write, "WRITE_SIZE", step_name)
     if not fs or not ws or not fc or not wc:

@@ -33,10 +33,11 @@ def _both(ctx, L, s, prec, call):
 
 
 # one row in the last tile and less than one tile (n = 6, 20, 70), one, two and
-# four rows a thread (n = 252, 924, 3432), segments from n = 12870 on
+# four rows a thread (n = 252, 924, 3432), segments from n = 12870 on, their sums
+# through one more launch (L = 24)
 # (J2 needs L >= 6)
 @pytest.mark.parametrize("J2,L", [(0.0, 4)] + [
-    (J2, L) for J2 in (0.0, 0.7) for L in (6, 8, 10, 12, 14, 16, 18, 20)])
+    (J2, L) for J2 in (0.0, 0.7) for L in (6, 8, 10, 12, 14, 16, 18, 20)] + [(0.7, 24)])
 def test_bounds_equal_the_step_kernel_run(ctx, pf, L, J2):
     """A few steps, before rounding has grown: every bound within steps * n
     roundings of the spectrum's width of the other run's."""
