@@ -1,6 +1,6 @@
-"""The one-workgroup Jacobi at its edges: odd and even sizes around the largest
-with its vectors in LDS and the largest of all, scaled far from 1, and the
-entropies' block launch on blocks of every size."""
+"""The one-workgroup Jacobi at its edges: odd and even sizes up to the
+largest, scaled far from 1, both sizes of its rotation log, and the entropies'
+block launch on blocks of every size."""
 
 import numpy as np
 import pytest
