@@ -59,12 +59,14 @@ __device__ __forceinline__ D2 pair_load(const double *p, int left) {
 // columns, as pairs (c, c + 1) or (PAIR false) singly.  Columns past the last
 // one are read from within the row instead (what they give goes to rows or
 // columns of the result that are not stored); of a pair that straddles the
-// end, the one before it is read and its second value taken.
-template <bool PAIR>
+// end, the one before it is read and its second value taken.  OFF: uint32_t
+// where a lane's offset over four rows and the columns is below 4 GB (one
+// address register a load), else uint64_t.
+template <bool PAIR, class OFF>
 struct GramSide {
   const char *base;   // of the row that comes next (scalar)
   long long step;     // bytes of four rows (scalar)
-  uint32_t off;       // this lane's bytes: its row of the four, its column
+  OFF off;            // this lane's bytes: its row of the four, its column
   bool second;
   __device__ __forceinline__ GramSide() {}
   __device__ __forceinline__ GramSide(const double *M, long long ld, long long row, int cols,
@@ -73,13 +75,13 @@ struct GramSide {
     second = PAIR && c > at;
     base = reinterpret_cast<const char *>(M + row * ld);
     step = 32 * ld;
-    off = (uint32_t)(8 * (kk * ld + at));
+    off = (OFF)(8 * (kk * ld + at));
   }
   __device__ __forceinline__ D2 fix(D2 v) const {
     if (PAIR && second) v[0] = v[1];
     return v;
   }
-  __device__ __forceinline__ D2 at(const char *row, uint32_t lane) const {
+  __device__ __forceinline__ D2 at(const char *row, OFF lane) const {
     D2 v;
     if (PAIR)
       v = *reinterpret_cast<const D2 *>(row + lane);
@@ -91,13 +93,13 @@ struct GramSide {
   __device__ __forceinline__ D2 get(int s) const { return at(base + s * step, off); }
   // the last rows, `left` of the four: the others zero
   __device__ __forceinline__ D2 tail(int kk, int left, long long ld) const {
-    D2 v = at(base, kk < left ? off : (uint32_t)(off - 8 * kk * ld));
+    D2 v = at(base, kk < left ? off : (OFF)(off - 8 * kk * ld));
     if (kk >= left) v = (D2){0.0, 0.0};
     return fix(v);
   }
 };
 
-template <int NB, int WM, int WN, bool PX>
+template <int NB, int WM, int WN, bool PX, class OFF = uint32_t>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_gram(
     long long n, int p, int q, const double *X, long long ldx, const double *Y, long long ldy,
     double *part, long long rows_per_chunk, int tiles_m, int tiles_n) {
@@ -127,8 +129,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     for (int v = 0; v < NB; ++v) acc[u][v] = (d4){0.0, 0.0, 0.0, 0.0};
 
   if (x0 < p && y0 < q && r0 < r1) {
-    GramSide<PX> sx(X, ldx, r0, p, x0 + 2 * i16, kk);
-    GramSide<(NB > 1)> sy(Y, ldy, r0, q, y0 + (NB == 1 ? i16 : 2 * i16), kk);
+    GramSide<PX, OFF> sx(X, ldx, r0, p, x0 + 2 * i16, kk);
+    GramSide<(NB > 1), OFF> sy(Y, ldy, r0, q, y0 + (NB == 1 ? i16 : 2 * i16), kk);
     struct Rows {
       D2 a[RS], b[RS];
     };
@@ -260,11 +262,20 @@ void launch_gram_parts(hipStream_t st, long long n, int p, int q, const double *
                        double *part, long long rows_per_chunk, long long nchunks) {
   int wm, wn, tiles_m, tiles_n;
   gram_tiles(p, q, wm, wn, tiles_m, tiles_n);
+  // rows so far apart that a lane's offset passes 32 bits (there are few of
+  // them): the smallest tile, with 64-bit offsets
+  const bool far = 8.0 * (3.0 * (double)std::max(ldx, ldy) + std::max(p, q)) >= 4294967296.0;
+  if (far) {
+    tiles_m = (p + 31) / 32;
+    tiles_n = (q + 15) / 16;
+  }
   const unsigned nblk = (unsigned)(nchunks * tiles_m * tiles_n);
   auto go = [&](auto kernel) {
     kernel<<<nblk, 256, 0, st>>>(n, p, q, X, ldx, Y, ldy, part, rows_per_chunk, tiles_m, tiles_n);
   };
-  if (q <= 16) {
+  if (far) {
+    p < 2 ? go(k_gram<1, 1, 1, false, uint64_t>) : go(k_gram<1, 1, 1, true, uint64_t>);
+  } else if (q <= 16) {
     if (p < 2)
       go(k_gram<1, 1, 1, false>);
     else
