@@ -23,6 +23,10 @@ void stage_apply_h(polfed_ctx *ctx, const Chain &c, int nvec, const T *X, T *Y);
 template <class T>
 void stage_apply_filter(polfed_ctx *ctx, const Chain &c, double E0, double E1, double sigma,
                         long long K, int nvec, const T *X, T *Y);
+template <class T>
+void stage_filter_batch(polfed_ctx *ctx, const std::vector<std::unique_ptr<Chain>> &chains,
+                        const double *E0, const double *E1, const double *sigma,
+                        const long long *K, int nvec, const T *const *X, T *const *Y);
 
 void check_launch(const char *what) {
   hipError_t e = hipGetLastError();
@@ -403,6 +407,39 @@ int polfed_apply_filter(polfed_ctx *ctx, const polfed_model *m, double E0, doubl
       stage_apply_filter<float>(ctx, c, E0, E1, sigma, K, nvec, static_cast<const float *>(X),
                                 static_cast<float *>(Y));
     PF_HIP(hipStreamSynchronize(ctx->stream));
+    return POLFED_OK;
+  });
+}
+
+// Not part of the ABI, for tests: the filters of R chains of one bond set
+// (all J2 zero or none) in the shared launches of polfed_solve_batch, each to
+// what polfed_apply_filter gives for it.  Arrays of R; X[r], Y[r] device
+// blocks as there.  Blocks until done.
+int polfed_test_filter_batch(polfed_ctx *ctx, int R, const polfed_model *models, const double *E0,
+                             const double *E1, const double *sigma, const long long *K,
+                             int precision, int nvec, const void *const *X, void *const *Y) {
+  return guarded(ctx, [&] {
+    PF_REQUIRE(R >= 1 && models && E0 && E1 && sigma && K && X && Y, "need R >= 1 and no NULL");
+    PF_REQUIRE(precision == 0 || precision == 1, "precision must be 0 or 1");
+    PF_REQUIRE(pow2_block(nvec), "nvec must be a power of two in [1, 64]");
+    std::vector<std::unique_ptr<Chain>> chains;
+    for (int r = 0; r < R; ++r) {
+      PF_REQUIRE(X[r] && Y[r] && X[r] != Y[r], "X, Y must be distinct non-NULL device pointers");
+      PF_REQUIRE(E1[r] > E0[r], "E1 must exceed E0");
+      PF_REQUIRE(std::fabs(sigma[r]) < 1.0, "|sigma_tilde| must be < 1");
+      PF_REQUIRE(K[r] >= 0 && K[r] <= (1LL << 26), "K must be in [0, 2^26]");
+      PF_REQUIRE((models[r].J2 != 0.0) == (models[0].J2 != 0.0), "one bond set only");
+      chains.emplace_back(new Chain());
+      make_chain(ctx, &models[r], *chains.back());
+    }
+    if (precision == 0)
+      stage_filter_batch<double>(ctx, chains, E0, E1, sigma, K, nvec,
+                                 reinterpret_cast<const double *const *>(X),
+                                 reinterpret_cast<double *const *>(Y));
+    else
+      stage_filter_batch<float>(ctx, chains, E0, E1, sigma, K, nvec,
+                                reinterpret_cast<const float *const *>(X),
+                                reinterpret_cast<float *const *>(Y));
     return POLFED_OK;
   });
 }

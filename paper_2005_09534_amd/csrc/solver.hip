@@ -1700,6 +1700,21 @@ struct FilterMember {
   const double *coef;  // device
   double c0, cK, Dinv;
   T w1, w2, w1f, w2f;
+  // the filter sum_k coef_k T_k(a H + b) / D (its coefficients also at `dev`);
+  // each weight rounded once, as in run_filter
+  void set_filter(const Chain &ch, double a, const std::vector<double> &host, double D,
+                  const double *dev) {
+    c = &ch;
+    coef = dev;
+    K = (long long)host.size() - 1;
+    c0 = host.front();
+    cK = host.back();
+    Dinv = 1.0 / D;
+    w1 = (T)(a * ch.J1);
+    w2 = (T)(a * ch.J2);
+    w1f = (T)(0.5 * (a * ch.J1) * Dinv);
+    w2f = (T)(0.5 * (a * ch.J2) * Dinv);
+  }
 };
 
 // What a batched filter's launches read from the host: alive until they are
@@ -1854,21 +1869,12 @@ static void refine_batched(polfed_ctx *ctx, std::vector<std::unique_ptr<Realizat
           PF_HIP(hipMemcpyAsync(coefs + co, r.coef_r.data(), sizeof(double) * r.coef_r.size(),
                                 hipMemcpyHostToDevice, st));
           FilterMember<double> m;
-          m.c = &r.c;
+          m.set_filter(r.c, r.a, r.coef_r, r.D_r, coefs + co);
           m.dt = r.dt64b.template as<double>();
           m.X = r.Vnb.template as<double>() + c0;
           m.Y = r.URb.template as<double>() + c0;
           m.ldx = m.ldy = r.ldr;
           m.buf = cheb + bo;
-          m.coef = coefs + co;
-          m.K = r.K_r;
-          m.c0 = r.coef_r[0];
-          m.cK = r.coef_r[r.K_r];
-          m.Dinv = 1.0 / r.D_r;
-          m.w1 = r.a * r.c.J1;
-          m.w2 = r.a * r.c.J2;
-          m.w1f = 0.5 * m.w1 * m.Dinv;
-          m.w2f = 0.5 * m.w2 * m.Dinv;
           mem.push_back(m);
           co += r.coef_r.size();
           bo += (size_t)3 * r.n * w;
@@ -1980,21 +1986,12 @@ static int solve_batch_impl(polfed_ctx *ctx, int R, const polfed_model *models,
       PF_HIP(hipMemcpyAsync(coefs.as<double>() + co, r.coef.data(), sizeof(double) * r.coef.size(),
                             hipMemcpyHostToDevice, st));
       FilterMember<T> &m = members[i];
-      m.c = &r.c;
+      m.set_filter(r.c, r.a, r.coef, r.D, coefs.as<double>() + co);
       m.dt = r.dt();
       m.X = r.Xs();
       m.Y = r.Ys();
       m.ldx = m.ldy = S;
       m.buf = cheb.as<T>() + bo;
-      m.coef = coefs.as<double>() + co;
-      m.K = r.K;
-      m.c0 = r.coef[0];
-      m.cK = r.coef[r.K];
-      m.Dinv = 1.0 / r.D;
-      m.w1 = (T)(r.a * r.c.J1);
-      m.w2 = (T)(r.a * r.c.J2);
-      m.w1f = (T)(0.5 * (double)m.w1 * m.Dinv);
-      m.w2f = (T)(0.5 * (double)m.w2 * m.Dinv);
       co += r.coef.size();
       bo += (size_t)3 * r.n * S;
     }
@@ -2296,6 +2293,53 @@ void stage_apply_filter(polfed_ctx *ctx, const Chain &c, double E0, double E1, d
   run_filter<T>(ctx, c, dt, a, nvec, X, nvec, Y, nvec, K, coef, D, bufs, sizeof(T) == 4, nullptr);
 }
 
+template <class T>
+void stage_filter_batch(polfed_ctx *ctx, const std::vector<std::unique_ptr<Chain>> &chains,
+                        const double *E0, const double *E1, const double *sigma,
+                        const long long *K, int nvec, const T *const *X, T *const *Y) {
+  const size_t R = chains.size();
+  std::vector<std::vector<double>> coef(R);
+  std::vector<double> D(R);
+  size_t rows = 0, ncoef = 0;
+  for (size_t r = 0; r < R; ++r) {
+    cheb_coeffs(sigma[r], K[r], coef[r], D[r], ctx->filter_damping);
+    rows += (size_t)chains[r]->basis->n;
+    ncoef += coef[r].size();
+  }
+  T *dt = static_cast<T *>(ctx->buf("stage_dt").ensure(sizeof(T) * rows));
+  T *buf = static_cast<T *>(ctx->buf("stage_cheb").ensure(sizeof(T) * 3 * rows * nvec));
+  double *dc = static_cast<double *>(ctx->buf("res_coef").ensure(sizeof(double) * ncoef));
+  std::vector<FilterMember<T>> mem(R);
+  for (size_t r = 0; r < R; ++r) {
+    const Chain &c = *chains[r];
+    const long long n = c.basis->n;
+    const double a = 2.0 / (E1[r] - E0[r]), b = -(E0[r] + E1[r]) / (E1[r] - E0[r]);
+    launch_scaled_diag<T>(ctx->stream, n, c.diag.as<double>(), a, b, dt);
+    PF_HIP(hipMemcpyAsync(dc, coef[r].data(), sizeof(double) * coef[r].size(),
+                          hipMemcpyHostToDevice, ctx->stream));
+    mem[r].set_filter(c, a, coef[r], D[r], dc);
+    mem[r].dt = dt;
+    mem[r].X = X[r];
+    mem[r].Y = Y[r];
+    mem[r].ldx = mem[r].ldy = nvec;
+    mem[r].buf = buf;
+    dt += n;
+    buf += (size_t)3 * n * nvec;
+    dc += coef[r].size();
+  }
+  FilterBatch<T> hold;
+  run_filter_batch<T>(ctx, mem, nvec, chains[0]->J2 != 0.0, hold);
+  PF_HIP(hipStreamSynchronize(ctx->stream));
+}
+
+template void stage_filter_batch<float>(polfed_ctx *, const std::vector<std::unique_ptr<Chain>> &,
+                                        const double *, const double *, const double *,
+                                        const long long *, int, const float *const *,
+                                        float *const *);
+template void stage_filter_batch<double>(polfed_ctx *, const std::vector<std::unique_ptr<Chain>> &,
+                                         const double *, const double *, const double *,
+                                         const long long *, int, const double *const *,
+                                         double *const *);
 template void stage_apply_h<float>(polfed_ctx *, const Chain &, int, const float *, float *);
 template void stage_apply_h<double>(polfed_ctx *, const Chain &, int, const double *, double *);
 template void stage_apply_filter<float>(polfed_ctx *, const Chain &, double, double, double,
