@@ -6,11 +6,9 @@ Two choices are tuned, both through the C ABI of libpolfed:
   16-byte loads per lane, persistent groups per CU, rank tables in LDS,
   streamed loads before or after the neighbour gathers, neighbour ranks from
   the tables, incrementally or from the stored pattern, column slices across
-  the XCDs) for a (chain
-  length L, block width,
-  precision): each candidate applies the filter for a few dozen steps to a
-  random block of the chain and is timed with the library's HIP-event
-  counters; the fastest shape per HBM-second wins
+  the XCDs) for a (chain length L, block width, precision): each candidate
+  runs a few dozen steps on a random block of the chain in a form that takes
+  its shape and is timed with the library's HIP-event counters
   (``polfed_set_step_shape``);
 * the filter recurrence (Clenshaw or the forward form, ``tune_form``): the
   same filter applied both ways, the shorter time wins
@@ -75,59 +73,91 @@ def staged_candidates(best, width):
             for (t, lpl, wpc) in LAUNCH for xcd in (2, 4, 8) if xcd <= width]
 
 
+def _random_block(n, width, precision):
+    """A random block on the GPU and one of its kind for the result."""
+    import torch
+    X = torch.randn((n, width), device="cuda", dtype=torch.float64)
+    X = X.to(torch.float32 if precision else torch.float64)
+    return X, torch.empty_like(X)
+
+
 def tune_shape(ctx, chain, width, precision, steps=None, shapes=None, cache=None, margin=0.03):
     """Fastest step-kernel shape for the chain's L at this width/precision.
 
+    Shapes with the rank tables (rank mode 0) are compared by the forward
+    form, whose steps take them; the Clenshaw filter with rank mode 0 chooses
+    its launches by size alone and would time the same kernel for each.  The
+    winner's Clenshaw filter, one figure, is then compared with those of the
+    other rank modes, which do run the step kernel.  With the forward form in
+    force (``ctx.set_filter_form``) all are compared by it.
+
     With `shapes` given, every candidate in it is timed.  By default the
-    search has two stages: every unsliced shape, then the launch shapes with
-    2, 4 and 8 column slices around the best of the first stage.  The shape
-    in force (the library default, or an earlier choice) is kept unless
-    another is faster by more than `margin`, so that near-ties do not flip
-    the choice from run to run.  Leaves the choice set on ctx; returns
-    (shape, GB/s)."""
-    import torch
+    tables' candidates are the launch shapes, with the column slices in force;
+    the other rank modes' every unsliced shape, then the launch shapes with 2,
+    4 and 8 column slices around the best of these.  The shape in force (the
+    library default, or an earlier choice) is kept unless another is faster by
+    more than `margin`, so that near-ties do not flip the choice from run to
+    run.  Leaves the choice set on ctx; returns (shape, GB/s of its filter)."""
     from . import polfed as pf
     m = pf.make_model(chain.L, chain.J1, chain.J2, chain.Delta, chain.h)
     n = pf.dim(chain.L)
-    dt = torch.float32 if precision else torch.float64
-    X = torch.randn((n, width), device="cuda", dtype=torch.float64).to(dt)
-    Y = torch.empty_like(X)
+    X, Y = _random_block(n, width, precision)
     if steps is None:
         steps = max(8, min(200, int(2e9 / (n * width * (4 if precision else 8) * 4))))
     E0, E1 = -2.0 * chain.L, 2.0 * chain.L  # any enclosing interval; cost is independent of it
+    current = tuple(ctx.get_step_shape(chain.L, width, precision))
+    form = ctx.filter_form
 
-    def rate(sh):
+    def timed(sh, by):
         ctx.set_step_shape(chain.L, width, precision, *sh)
+        ctx.set_filter_form(by)
         ctx.apply_filter(m, E0, E1, 0.0, 2, X, out=Y)
         ctx.filter_stats(reset=True)
         ctx.apply_filter(m, E0, E1, 0.0, steps, X, out=Y)
-        st = ctx.filter_stats(reset=True)
-        return st["bytes"] / st["gpu_s"] / 1e9
+        return ctx.filter_stats(reset=True)
 
-    current = tuple(ctx.get_step_shape(chain.L, width, precision))
-    best = (current, rate(current))
-    seen = {current}
+    seen = {}
 
-    def search(cands):
-        nonlocal best
+    def search(cands, by, best=None):
+        """(shape, seconds) of the fastest of cands and best."""
         for sh in cands:
             sh = tuple(sh)
-            if sh in seen:
+            if (sh, by) in seen:
                 continue
-            seen.add(sh)
-            gbs = rate(sh)
-            if gbs > best[1] * (1.0 + margin if best[0] == current else 1.0):
-                best = (sh, gbs)
+            t = seen[sh, by] = timed(sh, by)["gpu_s"]
+            if best is None or t * (1.0 + margin if best[0] == current else 1.0) < best[1]:
+                best = (sh, t)
+        return best
 
-    if shapes is not None:
-        search(shapes)
+    def among(cands, by):
+        return search(cands, by, search([current], by) if current in cands else None)
+
+    given = [tuple(sh) for sh in shapes] if shapes is not None else SHAPES
+    given = [current] + [sh for sh in given if sh != current]
+    if form == pf.FORM_FORWARD:  # (never sliced)
+        best = among([sh for sh in given if shapes is not None or sh[6] == current[6]], form)[0]
     else:
-        search([sh for sh in SHAPES if sh[6] == 1])
-        search(staged_candidates(best[0], width))
-    ctx.set_step_shape(chain.L, width, precision, *best[0])
+        tables = [sh for sh in given
+                  if sh[5] == 0 and (shapes is not None or sh[6] == current[6])]
+        others = [sh for sh in given if sh[5] != 0 and (shapes is not None or sh[6] == 1)]
+        if current[5] != 0 and current not in others:
+            others.append(current)
+        tab = among(tables, pf.FORM_FORWARD) if tables else None
+        oth = among(others, form) if others else None
+        if oth is not None and shapes is None:
+            oth = search(staged_candidates(oth[0], width), form, oth)
+        if tab is None or oth is None:
+            best = (tab or oth)[0]
+        else:
+            # the one in force has the margin on its side
+            t_tab = timed(tab[0], form)["gpu_s"]
+            f_tab, f_oth = (1.0 + margin, 1.0) if current[5] != 0 else (1.0, 1.0 + margin)
+            best = tab[0] if t_tab * f_tab < oth[1] * f_oth else oth[0]
+    st = timed(best, form)
+    gbs = st["bytes"] / st["gpu_s"] / 1e9
     if cache is not None:
-        cache[_key("shape", chain.L, chain.J2, precision, width)] = list(best[0]) + [best[1]]
-    return best
+        cache[_key("shape", chain.L, chain.J2, precision, width)] = list(best) + [gbs]
+    return best, gbs
 
 
 def tune_form(ctx, chain, width, precision, K=None, margin=0.03):

@@ -282,6 +282,7 @@ class Context:
             raise PolfedError(rc, f"polfed_create({device}) failed: {msg}")
         self.h = h
         self.device = device
+        self.filter_form = FORM_CLENSHAW  # (the library's default)
         self.bind_stream()
 
     def bind_stream(self, stream=None):
@@ -428,6 +429,7 @@ class Context:
     def set_filter_form(self, form):
         """FORM_CLENSHAW (default) or FORM_FORWARD."""
         self._check(LIB.polfed_set_filter_form(self.h, int(form)), "set_filter_form")
+        self.filter_form = int(form)
 
     def filter_stats(self, reset=True):
         g, l, b = c_double(), c_double(), c_double()
