@@ -227,26 +227,6 @@ def tune_block(ctx, chains, nev, precision, widths=(4, 8, 16, 32), cache=None, s
             return st, (time.perf_counter() - t0) / len(models)
         run()  # warm (graph capture, buffers)
         st, t = timed()
-        if len(models) > 1:
-            # batches have shapes of their own, kept and reported (the batched
-            # kernels choose their launches by size alone): re-time the
-            # groups-per-CU entry on the sample batch, keep a change only when
-            # it gains more than 3%
-            base = tuple(ctx.get_batch_shape(L, s, precision))
-            best_sh, best_st, best_t = base, st, t
-            for wpc in (2, 4, 8, 16):
-                sh = (base[0], base[1], wpc) + base[3:]
-                if wpc == base[2] or wpc * base[0] > 2048:
-                    continue
-                ctx.set_batch_shape(L, s, precision, *sh)
-                run()
-                st_w, t_w = timed()
-                if all(x == pf.OK for x in st_w) and t_w < best_t * 0.97:
-                    best_sh, best_st, best_t = sh, st_w, t_w
-            ctx.set_batch_shape(L, s, precision, *best_sh)
-            if shape_cache is not None and best_sh != base:
-                shape_cache[_key("bshape", L, chains[0].J2, precision, s)] = list(best_sh) + [0.0]
-            st, t = best_st, best_t
         if all(x == pf.OK for x in st):
             times[s] = t
             if best is None or t < best[1]:

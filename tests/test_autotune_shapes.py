@@ -94,3 +94,33 @@ def test_given_shapes_are_all_timed():
     ctx = _Ctx(_forward(given[1]), lambda sh: 0.5 if sh[5] == 0 else 2.0)
     assert autotune.tune_shape(ctx, workloads.chain(12, 2.0, 1), 8, 0, shapes=given)[0] == given[1]
     assert set(given) <= {s for s, _ in ctx.calls}
+
+
+def test_blocks_of_a_batch_are_timed_once_each(monkeypatch):
+    """The batched filters take no launch shape: a width's sample batch runs to
+    warm up and once timed, and no shape is set or kept."""
+    import torch
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a: None)
+
+    class Batch:
+        runs, blocks = [], []
+
+        def get_batch_shape(self, L, nvec, precision):
+            return CURRENT[:5] + (1,)
+
+        def solve_batch(self, models, nev, block_size, precision, vectors):
+            self.runs.append(block_size)
+            return dict(status=[pf.OK] * len(models))
+
+        def set_block_size(self, L, precision, nev, block_size):
+            self.blocks.append(block_size)
+
+        def set_batch_shape(self, *a):
+            raise AssertionError("a batch shape was set")
+
+    ctx, shapes, blocks = Batch(), {}, {}
+    chains = [workloads.chain(12, 2.0, r) for r in range(3)]
+    best = autotune.tune_block(ctx, chains, 20, 1, widths=(4, 8), cache=blocks, shape_cache=shapes)
+    assert ctx.runs == [4, 4, 8, 8] and shapes == {}
+    assert best[0] in (4, 8) and ctx.blocks == [best[0]]
+    assert blocks[autotune._key("block", 12, 0.0, 1, 20)][0] == best[0]
