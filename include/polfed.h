@@ -322,7 +322,10 @@ int polfed_bounds(polfed_ctx *ctx, const polfed_model *model, int steps,
  * x % xcd_slices over 8 / xcd_slices of the rows, so that each XCD's L2
  * holds more rows of a narrower slice; the Clenshaw filter then keeps its
  * recurrence blocks slice-major; a width that does not split runs
- * unsliced; single H applications and the forward form are never sliced).
+ * unsliced; the forward form is never sliced; single H applications with
+ * rank_incremental = 0 to blocks beyond the L2 caches go in slices of whole
+ * 128-byte lines, at most xcd_slices of them where there is an entry, and
+ * are not sliced with rank_incremental 1 or 2).
  * Results are identical for every shape.  With rank_incremental = 0 the
  * Clenshaw filter chooses its launches by size alone (chains up to L = 14
  * whole in LDS, longer ones by segments of the basis), and the other fields

@@ -284,20 +284,37 @@ static bool use_segments(const StepShape &shape, int L) {
   return shape.rank_incr == 0 && L >= kSegM + 4;
 }
 
+// Column slices of a product with H that the step kernel does by rows, rank
+// tables: XCD x works on slice x % slices, so its L2 holds more rows of what it
+// gathers from.  Slices of 128 bytes of a row, a whole line, with J2; of 256
+// without, where a row has half the gathers; 1 for rows of no more than that
+// and for blocks that the L2s (8 x 4 MB) hold.  Smaller slices read every line
+// once for each of its slices.  One product, us, in 1, 2 and 4 slices:
+//   J1-J2, 64 FP64 columns: L = 18   57   56   57; L = 20  180  174  171;
+//                 L = 22  980  886  861; L = 24 4182 3869 3854; L = 26 19.2 18.2 17.6 ms
+//   J1-J2, 32 FP64 columns: L = 22  397  379  694; L = 24 1937 1819 3204
+//   J1-J2, 64 FP32 columns: L = 22  371  352  643; L = 24 1966 1832 3414
+//   XXZ,   64 FP64 columns: L = 22  545  513  533; L = 24 2256 2132 2200
+//   XXZ,   32 FP64 columns: L = 22  262  251  404; L = 26 5006 5096 8197
+// An entry of the context may ask for fewer.
+static int product_slices(const polfed_ctx *ctx, const StepShape &shape, const Chain &c, int S,
+                          int elem) {
+  if (shape.rank_incr != 0 || (double)c.basis->n * S * elem <= 32e6) return 1;
+  const int ns = std::max(1, S * elem / (c.J2 != 0.0 ? 128 : 256));
+  const bool entry = ctx->shapes.count(std::make_tuple(c.L, S, elem)) != 0;
+  return entry ? std::min(ns, shape.xcd_slices) : ns;
+}
+
 // out = scale * (dt .* V + sum w_l V[nbr]) for a block of `width` columns,
 // split into power-of-two chunks of at most 64 columns.  A block of one slice
 // goes by segments in place (one FP64 column: L = 16 25 us a call against 30,
 // L = 24 109 against 160); wider ones would have to be packed and unpacked for
 // the one product (L = 22, 64 FP64 columns: 687 us against 536) and take the
-// step kernel's tables, J1-J2 FP64 blocks beyond the Infinity Cache in four
-// column slices over the XCDs (64 FP64 columns, L = 22: 872 us against 967,
-// L = 24: 3.82 ms against 4.17; without J2 625 against 540, FP32 and smaller
-// blocks slower as well).
+// step kernel.
 template <class T>
 static void apply_op(polfed_ctx *ctx, const Chain &c, const T *dt, double wscale1,
                      double wscale2, const T *V, long long ldv, T *out, long long ldo, int width,
                      bool fp32) {
-  const long long n = c.basis->n;
   int off = 0;
   while (off < width) {
     int S = 64;
@@ -326,10 +343,8 @@ static void apply_op(polfed_ctx *ctx, const Chain &c, const T *dt, double wscale
     a.dscale = T(1);
     a.w1 = (T)wscale1;
     a.w2 = (T)wscale2;
-    if (sizeof(T) == 8 && S == 64 && c.J2 != 0.0 && (double)n * 512.0 > 256e6) {
-      a.nslices = 4;
-      a.vss = a.oss = S / 4;
-    }
+    a.nslices = product_slices(ctx, shape, c, S, (int)sizeof(T));
+    a.vss = a.oss = S / a.nslices;
     launch_step<T>(ctx->stream, S, a, shape, ctx->num_cu);
     off += S;
   }
