@@ -310,18 +310,40 @@ void launch_gram(hipStream_t st, long long n, int p, int q, const double *X, lon
 // ---------------------------------------------------------------- update --
 //
 // Y = alpha X C + beta Y.  A wave owns 16 rows and all q <= 64 columns (NB
-// tiles of 16); the sum over k goes in blocks of 64, whose rows of C are
+// tiles of 16); the sum over k goes in blocks of KU, whose rows of C are
 // staged in LDS once for the workgroup's NW waves (row stride = 16 mod 32
 // doubles: the four rows of an MFMA step in different banks).  Lane l = (i =
 // l%16, kk = l/16) reads X[row i][16 s + 4 kk .. + 3] of the block, so the four
 // lanes of a row take a whole 128-byte line between them, and the k of MFMA
 // step (s, e) is 16 s + 4 kk + e for both operands.  The next block's X is
-// loaded while this one's is multiplied.  Bound by reading X.  With 8-byte
-// loads of 4 k at a time and C from L1: n = 705,432, p = 480, q = 32 1235 us,
-// n = 3,432, p = 104, q = 8 a call of 21 us; so 752 (4.1 TB/s) and 18.
+// loaded while this one's is multiplied.  Bound by reading X, so by how many
+// waves a SIMD holds: blocks of 64 left four of them (and 31 idle columns of 64
+// at p = 33), blocks of 16 six to eight; with one tile of Y there is room for
+// 32.  n = 705,432, us a launch with blocks of 64, 32, 16 (and, before there
+// was any staging, with 8-byte loads of 4 k at a time and C from L1):
+//   p =  33, q =  8:   73   51   49  (56)    p =  33, q = 64:  283  278  220  (251)
+//   p =  64, q =  8:  103   81   90 (131)    p =  64, q = 32:  181  152  140  (211)
+//   p = 480, q =  8:  571  540  577 (954)    p = 480, q = 32:  727  664  643 (1222)
 
-// KU: k of a block (64; 32 and 16 where p is no more, so that short sums
-// stage and load no padding).
+// The wave's tiles: component v of lane l is element (l/16 + 4v, l%16).
+template <int NB>
+__device__ __forceinline__ void update_store(long long n, int q, double alpha, const d4 (&acc)[NB],
+                                             double beta, double *Y, long long ldy,
+                                             long long row0, int i16, int kk) {
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int j = u * 16 + i16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const long long row = row0 + kk + 4 * v;
+      if (row < n && j < q) {
+        double *y = Y + row * ldy + j;
+        *y = (beta == 0.0) ? alpha * acc[u][v] : alpha * acc[u][v] + beta * (*y);
+      }
+    }
+  }
+}
+
 template <int NB, int NW, int KU>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_update(
     long long n, int p, int q, double alpha,
@@ -373,18 +395,36 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
           acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(
               b[s][e / 2][e % 2], sc[(16 * s + 4 * kk + e) * kLd + 16 * u + i16], acc[u], 0, 0, 0);
   }
+  update_store<NB>(n, q, alpha, acc, beta, Y, ldy, row0, i16, kk);
+}
+
+// Sums of up to 8 terms: C straight from the caches; staging it and the barrier
+// take longer than they save (n = 705,432, p = 1, a launch: q = 1 14.7 us
+// against 16.5, q = 64 142 against 157).
+template <int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_update_short(long long n, int p, int q, double alpha,
+                                                          const double *X, long long ldx,
+                                                          const double *C, long long ldc,
+                                                          double beta, double *Y, long long ldy) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const long long row0 = ((long long)blockIdx.x * NW + wave) * 16;
+  const int i16 = lane & 15, kk = lane >> 4;
+  const long long ra = row0 + i16;
+  d4 acc[NB];
 #pragma unroll
-  for (int u = 0; u < NB; ++u) {
-    const int j = u * 16 + i16;
+  for (int u = 0; u < NB; ++u) acc[u] = (d4){0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 0; k0 < p; k0 += 4) {
+    const int k = k0 + kk;
+    const double a = (ra < n && k < p) ? X[ra * ldx + k] : 0.0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const long long row = row0 + kk + 4 * v;
-      if (row < n && j < q) {
-        double *y = Y + row * ldy + j;
-        *y = (beta == 0.0) ? alpha * acc[u][v] : alpha * acc[u][v] + beta * (*y);
-      }
+    for (int u = 0; u < NB; ++u) {
+      const int j = 16 * u + i16;
+      const double b = (k < p && j < q) ? C[(size_t)k * ldc + j] : 0.0;
+      acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[u], 0, 0, 0);
     }
   }
+  update_store<NB>(n, q, alpha, acc, beta, Y, ldy, row0, i16, kk);
 }
 
 void launch_update(hipStream_t st, long long n, int p, int q, double alpha, const double *X,
@@ -405,12 +445,18 @@ void launch_update(hipStream_t st, long long n, int p, int q, double alpha, cons
   };
   auto with_nb = [&](auto nb_c) {
     constexpr int NB = decltype(nb_c)::value;
-    if (p <= 16)
-      nw == 8 ? go(k_update<NB, 8, 16>) : go(k_update<NB, 4, 16>);
-    else if (p <= 32)
-      nw == 8 ? go(k_update<NB, 8, 32>) : go(k_update<NB, 4, 32>);
-    else
-      nw == 8 ? go(k_update<NB, 8, 64>) : go(k_update<NB, 4, 64>);
+    if (p <= 8) {
+      nw == 8 ? go(k_update_short<NB, 8>) : go(k_update_short<NB, 4>);
+      return;
+    }
+    // blocks of 32 where there is room (one tile of Y) and they are not half
+    // padding (p = 33, q = 8, n = 48,620: 7.0 us against 6.0 in blocks of 16)
+    if constexpr (NB == 1)
+      if (p > 48 || (p > 16 && p <= 32)) {
+        nw == 8 ? go(k_update<1, 8, 32>) : go(k_update<1, 4, 32>);
+        return;
+      }
+    nw == 8 ? go(k_update<NB, 8, 16>) : go(k_update<NB, 4, 16>);
   };
   if (q <= 16)
     with_nb(std::integral_constant<int, 1>{});
