@@ -44,7 +44,6 @@
 // Included by hv.hip (FP64 instantiations, casts) and hv_f32.hip (FP32
 // instantiations), which compile in parallel.
 #include <algorithm>
-#include <climits>
 #include <type_traits>
 
 #include "internal.h"
@@ -350,9 +349,8 @@ __global__ __launch_bounds__(MAXT) void k_step(StepArgs<T> a) {
 }
 
 // Calls f.template operator()<LDS_TAB, MAXT, EARLY, RM>() for the runtime
-// choice (rank modes other than the tables only where the launcher uses
-// them; the stored pattern needs no tables in LDS).
-template <bool MODES_USED, class F>
+// choice (the stored pattern needs no tables in LDS).
+template <class F>
 static void dispatch_shape(bool lds, int threads, bool early, int rank_mode, F &&f) {
   if (threads != 256 && threads != 512 && threads != 1024)
     throw Error(POLFED_EINVAL, "step kernel: threads must be 256, 512 or 1024");
@@ -360,10 +358,10 @@ static void dispatch_shape(bool lds, int threads, bool early, int rank_mode, F &
     constexpr bool LD = decltype(lds_c)::value;
     constexpr int TH = decltype(thr_c)::value;
     constexpr bool EA = decltype(early_c)::value;
-    if (MODES_USED && rank_mode == 1)
-      f.template operator()<LD, TH, EA, MODES_USED ? 1 : 0>();
-    else if (MODES_USED && rank_mode == 2)
-      f.template operator()<false, TH, EA, MODES_USED ? 2 : 0>();
+    if (rank_mode == 1)
+      f.template operator()<LD, TH, EA, 1>();
+    else if (rank_mode == 2)
+      f.template operator()<false, TH, EA, 2>();
     else
       f.template operator()<LD, TH, EA, 0>();
   };
@@ -383,8 +381,8 @@ static void dispatch_shape(bool lds, int threads, bool early, int rank_mode, F &
     early ? with_threads(F_{}, T_{}) : with_threads(F_{}, F_{});
 }
 
-// Launchers of the two step kernels for one (T, S, LPL), called by
-// dispatch_shape with the remaining template parameters.
+// Launcher of the step kernel for one (T, S, LPL), called by dispatch_shape
+// with the remaining template parameters.
 template <class T, int S, int LPL>
 struct StepLaunch {
   hipStream_t st;
@@ -425,8 +423,8 @@ static void launch_step_s(hipStream_t st, const StepArgs<T> &a0, const StepShape
   const bool lds = shape.lds_tables && a.L <= kMaxLdsTableL && mode != 2;
   const size_t shm =
       lds ? (size_t)6 * ((size_t)1 << a.half) + (mode == 1 ? sizeof(int32_t) * 32 * 32 : 0) : 0;
-  dispatch_shape<true>(lds, threads, shape.early_loads != 0, mode,
-                       StepLaunch<T, S, LPL>{st, a, nwg, threads, shm});
+  dispatch_shape(lds, threads, shape.early_loads != 0, mode,
+                 StepLaunch<T, S, LPL>{st, a, nwg, threads, shm});
   check_launch("k_step");
 }
 
