@@ -6,7 +6,7 @@
 // Each block of vectors r runs the forward recurrence t_0 = r, t_1 = H~ r,
 // t_{k+1} = 2 H~ t_k - t_{k-1} with the fused step kernel, and a
 // deterministic two-stage reduction takes <t_k, t_k> and <t_k, t_{k-1}> over
-// all rows and columns.  From L = 16 the steps run by segments (segment.hip)
+// all rows and columns.  From L = 14 the steps run by segments (segment.hip)
 // and leave their segments' sums themselves, many steps' sums added up by one
 // launch: L = 20, J1-J2, 4 vectors, a step and its sums took 29.4 us as step,
 // dot and final launches, 10.4 us so.  With T_{2k} = 2 T_k^2 - 1 and

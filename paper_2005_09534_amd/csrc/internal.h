@@ -311,7 +311,7 @@ void launch_gram(hipStream_t st, long long n, int p, int q, const double *X, lon
                  int num_cu);
 // The Gram product in its two launches, on partial tiles the caller
 // provides: gram_chunks picks the row chunks (about four workgroups per CU,
-// >= 256 rows each; cap > 0 limits them to cap / (p q) partial tiles) and
+// at least 64 rows a wave; cap > 0 limits them to cap / (p q) partial tiles) and
 // launch_gram_parts runs the MFMA kernel and the fixed-order chunk sum.
 long long gram_chunks(long long n, int p, int q, int num_cu, long long cap,
                       long long &rows_per_chunk);

@@ -51,7 +51,8 @@ __device__ __forceinline__ void jacobi_rotation(const double *A, int n, int m, i
   jacobi_angle(A, n, rr_index(k, r, m), rr_index(m - 1 - k, r, m), p, q, c, s);
 }
 
-// Largest matrix that fits (10 KB of LDS besides it).
+// Largest matrix the kernels are built for: 64 pairs, one for each lane of a
+// wave (its 132 KB and 4 KB of sums and rotations leave 24 KB of the LDS).
 constexpr int kLdsEigMax = 128;
 constexpr int kEigThreads = 1024;
 constexpr int kEigSweeps = 40;  // at most (about 8 are usual)

@@ -567,7 +567,8 @@ int resident_form(long long n, int elem) {
   return -1;
 }
 
-// Steps of one launch: 16384 steps of the longest chain here are about 0.1 s.
+// Steps of one launch: 16384 steps of the longest chain here (L = 16) are 0.12
+// s, with J2 0.22.
 constexpr long long kResSteps = 16384;
 
 long long resident_scratch(long long n, int elem) { return 4 * n + 64 / elem; }

@@ -19,8 +19,8 @@
 //
 // So no rank is computed in the kernel.  A record a segment holds the
 // uniform offsets (read with scalar loads) and a 16-byte record a low part
-// (32 with J2) the distances, as bytes: |distance| <= C(9, 4) = 126, the
-// places < C(10, 5) = 252.  Bonds add up in the order of the step kernel (J1
+// (32 with J2) the neighbours' places in their segments, as bytes: there are
+// at most C(10, 5) = 252.  Bonds add up in the order of the step kernel (J1
 // by ascending bit, then J2), so results are equal to its bit for bit.
 //
 // Blocks are slice-major: 16 bytes of a row to a slice (or the whole row where

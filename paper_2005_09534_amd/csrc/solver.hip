@@ -255,7 +255,7 @@ static double queue_filter(hipStream_t stream, int num_cu, const StepShape &shap
   st.X = Xin;
   st.ldx = ldxin;
   st.xss = xss;
-  // (products with 1/D, as in the batched kernel)
+  // (products with 1/D, as in the one-launch filter and the segments)
   const double Dinv = 1.0 / D;
   st.alpha = (T)(coef[0] * Dinv);
   if (K >= 1) {
@@ -277,9 +277,11 @@ static double queue_filter(hipStream_t stream, int num_cu, const StepShape &shap
   return moved;
 }
 
-// Whether the steps of a chain of length L run by segments (segment.hip):
-// above the resident filter's lengths, unless the shape asks for another rank
-// method than the tables.
+// Whether the steps of a chain of length L run by segments (segment.hip): from
+// L = 14 on (below, a high part is two sites and fewer), unless the shape asks
+// for another rank method than the tables.  At L = 14 the
+// Clenshaw filter and the bounds are one launch instead (use_resident), single
+// products and KPM moments take the segments.
 static bool use_segments(const StepShape &shape, int L) {
   return shape.rank_incr == 0 && L >= kSegM + 4;
 }
@@ -2228,8 +2230,8 @@ int solve_batch(polfed_ctx *ctx, int R, const polfed_model *models, const polfed
                 int *status) {
   polfed_opts o = resolve_opts(opts_in);
   PF_REQUIRE(R >= 1 && models && status && evals && resid, "invalid batch arguments");
-  // the batched kernel is Clenshaw's; the members' single-chain filters (the
-  // refinement) follow it, whatever the context's setting
+  // the batched filters are Clenshaw's; the members' single-chain filters (the
+  // refinement) follow them, whatever the context's setting
   struct FormGuard {
     polfed_ctx *c;
     int saved;
