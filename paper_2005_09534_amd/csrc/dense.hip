@@ -319,8 +319,9 @@ void launch_gram(hipStream_t st, long long n, int p, int q, const double *X, lon
 // loaded while this one's is multiplied.  Bound by reading X, so by how many
 // waves a SIMD holds: blocks of 64 left four of them (and 31 idle columns of 64
 // at p = 33), blocks of 16 six to eight; with one tile of Y there is room for
-// 32.  n = 705,432, us a launch with blocks of 64, 32, 16 (and, before there
-// was any staging, with 8-byte loads of 4 k at a time and C from L1):
+// 32 (launch_update has the rule).  n = 705,432, us a launch with blocks of 64,
+// 32, 16 (and, before there was any staging, with 8-byte loads of 4 k at a time
+// and C from L1):
 //   p =  33, q =  8:   73   51   49  (56)    p =  33, q = 64:  283  278  220  (251)
 //   p =  64, q =  8:  103   81   90 (131)    p =  64, q = 32:  181  152  140  (211)
 //   p = 480, q =  8:  571  540  577 (954)    p = 480, q = 32:  727  664  643 (1222)
@@ -438,7 +439,20 @@ void launch_update(hipStream_t st, long long n, int p, int q, double alpha, cons
     return;
   }
   // eight waves share a block of C where that still gives every CU work
-  const int nw = n >= 65536 ? 8 : 4;
+  const bool few = n < 65536;
+  const int nw = few ? 4 : 8;
+  // Blocks of k.  Many rows: 16, so that most waves share a SIMD, or 32 with one
+  // tile of Y, where that is not half padding.  Few rows: there are few waves,
+  // and what one has in flight counts for more; sums of up to 64 go in one block
+  // where it is filled, long ones in blocks of 32 and 64 (n = 12,870, q = 32, in
+  // blocks of 16, 32 and 64: p = 56 6.5, 6.3, 6.2 us; p = 80 7.4, 7.7, 8.9; p =
+  // 160 11.2, 10.6, 11.8; p = 640 56.7, 48.8, 47.5).
+  int ku = 16;
+  if (few ? (p > 16 && p <= 32) || (p >= 128 && p < 256)
+          : q <= 16 && ((p > 16 && p <= 32) || p > 48))
+    ku = 32;
+  else if (few && ((p > 48 && p <= 64) || p >= 256))
+    ku = 64;
   const unsigned nwg = (unsigned)((n + 16 * nw - 1) / (16 * nw));
   auto go = [&](auto kernel) {
     kernel<<<nwg, 64 * nw, 0, st>>>(n, p, q, alpha, X, ldx, C, ldc, beta, Y, ldy);
@@ -446,17 +460,16 @@ void launch_update(hipStream_t st, long long n, int p, int q, double alpha, cons
   auto with_nb = [&](auto nb_c) {
     constexpr int NB = decltype(nb_c)::value;
     if (p <= 8) {
-      nw == 8 ? go(k_update_short<NB, 8>) : go(k_update_short<NB, 4>);
+      few ? go(k_update_short<NB, 4>) : go(k_update_short<NB, 8>);
       return;
     }
-    // blocks of 32 where there is room (one tile of Y) and they are not half
-    // padding (p = 33, q = 8, n = 48,620: 7.0 us against 6.0 in blocks of 16)
+    if (few) {
+      ku == 16 ? go(k_update<NB, 4, 16>) : ku == 32 ? go(k_update<NB, 4, 32>) : go(k_update<NB, 4, 64>);
+      return;
+    }
     if constexpr (NB == 1)
-      if (p > 48 || (p > 16 && p <= 32)) {
-        nw == 8 ? go(k_update<1, 8, 32>) : go(k_update<1, 4, 32>);
-        return;
-      }
-    nw == 8 ? go(k_update<NB, 8, 16>) : go(k_update<NB, 4, 16>);
+      if (ku == 32) return go(k_update<1, 8, 32>);
+    go(k_update<NB, 8, 16>);
   };
   if (q <= 16)
     with_nb(std::integral_constant<int, 1>{});

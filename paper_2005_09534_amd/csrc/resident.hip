@@ -10,7 +10,7 @@
 //   L = 16, s = 64 FP32: 8.2 and 7.5, the same for every column a CU holds
 // What bounds it is the LDS gather: a row reads about L/2 + 1 neighbours at
 // scattered addresses, 5 cycles a read of 64 lanes (half of it bank conflicts;
-// LDS busy 92 % of the time at L = 14, 72 % at L = 16).
+// LDS busy 82 % of the launch at L = 14, 70 % at L = 16).
 //
 // Rows are held in an order of their own: sorted by the number of J1 bonds
 // that act on them (then J2 bonds, then row), so that the 64 rows of a

@@ -15,8 +15,10 @@ def ctx():
     c.close()
 
 
-# sums without staging (up to 8), one, two and three blocks of 16 and of 32
-@pytest.mark.parametrize("p", [3, 4, 7, 8, 9, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 97])
+# sums without staging (up to 8), one, two and three blocks of 16 and of 32, and
+# the limits from which few rows take blocks of 32 (128) and 64 (256)
+@pytest.mark.parametrize("p", [3, 4, 7, 8, 9, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64, 65, 97, 127, 128, 161,
+                               255, 256, 257, 320])
 @pytest.mark.parametrize("q", [1, 15, 16, 17, 32, 33, 64])
 @pytest.mark.parametrize("n", [37, 65541])
 def test_update_around_its_blocks(ctx, n, p, q):
