@@ -189,9 +189,11 @@ struct alignas(sizeof(T) * VE) Piece {
   T v[VE];
 };
 
+// (X, Y and the operand of a product are the caller's: aligned as their
+// elements are, no more.  The loads are the same.)
 template <class T, int VE, bool NT = false>
 __device__ __forceinline__ void piece_load(Gptr base, uint32_t off, T (&v)[VE]) {
-  typedef T VT __attribute__((ext_vector_type(VE)));
+  typedef T VT __attribute__((ext_vector_type(VE), aligned(sizeof(T))));
   const __attribute__((address_space(1))) VT *at =
       (const __attribute__((address_space(1))) VT *)(base + off);
   const VT p = NT ? __builtin_nontemporal_load(at) : *at;
@@ -200,7 +202,7 @@ __device__ __forceinline__ void piece_load(Gptr base, uint32_t off, T (&v)[VE]) 
 }
 template <class T, int VE, bool NT>
 __device__ __forceinline__ void piece_store(Gptr base, uint32_t off, const T (&v)[VE]) {
-  typedef T VT __attribute__((ext_vector_type(VE)));
+  typedef T VT __attribute__((ext_vector_type(VE), aligned(sizeof(T))));
   VT p;
 #pragma unroll
   for (int e = 0; e < VE; ++e) p[e] = v[e];
